@@ -169,7 +169,7 @@ struct Arrow1 {
 // f and f' at x > 0, with b1^2/x and b2^2/(x + ab) to about one ulp from a
 // single reciprocal of x (x + ab).
 struct Spec {
-  double f, fp, rx, rp, q2;
+  double f, fp, rx, rp, q1, q2;
 };
 
 __device__ __forceinline__ Spec spec_eval(const Arrow1& P, double x) {
@@ -183,6 +183,7 @@ __device__ __forceinline__ Spec spec_eval(const Arrow1& P, double x) {
   s.fp = __builtin_fma(q1, rx, __builtin_fma(q2, rp, 1.0));
   s.rx = rx;
   s.rp = rp;
+  s.q1 = q1;
   s.q2 = q2;
   return s;
 }
@@ -212,12 +213,6 @@ __device__ __forceinline__ double quad_zero(double c, double k, double a) {
 }
 
 constexpr int kChords = 2;
-// Chords of the FP32-storage form's start, before its one FP32 step.  In a
-// CPU emulation, the Newton step's check then sends 6% of SPD wavefronts
-// and 1% of N(0,1) ones to FP64 Borges-Gragg with three chords, 34% and 20%
-// with two; iterating FP32 to its own stop test instead takes a second
-// FP32 trip in 89% and 99% of wavefronts.
-constexpr int kChordsRefine = 3;
 
 __device__ __forceinline__ double bg_start(const Arrow1& P, double rab) {
   double U = quad_zero(P.gb, P.b1s + P.b2s, 1.0);
@@ -233,19 +228,21 @@ __device__ __forceinline__ double bg_start(const Arrow1& P, double rab) {
 }
 
 // FP32 versions (v_rcp_f32 and v_sqrt_f32 are accurate to about one ulp),
-// for the start of the FP64 iteration, for the FP32 start and step that the
-// FP32-storage form's Newton step refines, and for the FP32 zero finder of
-// the unrefined FP32 ablation.  The FP64 iteration's start only has to be
-// close: it converges from either side (bg_step), and a start within about
-// 1e-5 of the zero still needs a single evaluation of f in FP64.  FP32 is
-// cheaper than the FP64 sequences, and the FP64 path is limited as much by
-// the clock the chip sustains under FP64 load as by HBM.
-// c0 = gb + b2^2/ab and rab = 1/ab, formed in FP64 and rounded, for the two
-// FP32-storage forms' chords and steps (unused by start_point).
+// for the start of the FP64 zero finder and for the FP32 zero finder of the
+// unrefined FP32 ablation.  The start is where single precision pays: an
+// FP32 multiply, add or FMA takes half the issue time of an FP64 one
+// (measured: 2 against 4 cycles per wavefront), v_rcp_f32 and v_sqrt_f32
+// half that of v_rcp_f64 and v_rsq_f64 (8 against 16), and FP64 FMAs lower
+// the clock besides.
+// c0 = gb + b2^2/ab and rab = 1/ab are formed in FP64 and rounded.
 struct Arrow1f {
-  float b1s, b2s, ab, gb;
-  float c0 = 0.0f, rab = 0.0f;
+  float b1s, b2s, ab, gb, c0, rab;
 };
+
+__device__ __forceinline__ Arrow1f to_f32(const Arrow1& P, double rab) {
+  return Arrow1f{(float)P.b1s, (float)P.b2s, (float)P.ab, (float)P.gb,
+                 (float)__builtin_fma(P.b2s, rab, P.gb), (float)rab};
+}
 
 __device__ __forceinline__ float quad_zero32(float c, float k, float a) {
   const float c2 = 0.5f * c;
@@ -276,61 +273,66 @@ __device__ __forceinline__ float bg_start32(const Arrow1f& P) {
   return U;
 }
 
-// Start of the FP64 iteration, in FP32 from the arrow rounded to FP32: a
-// bracket [L, U] of the zero, narrowed twice, and its upper end.
-//  * L0 = the paper's Newton start (Sec. 1.4.2), the zero of x - gb - b1^2/x
-//    (the term b2^2/(x + ab) dropped), a lower bound; U0 = x_inf, an upper
-//    bound (see bg_start).
-//  * Chord of the convex 1/(x + ab) over [L, U]: it lies above the
-//    function there, so x - gb - b1^2/x - b2^2 chord(x) lies below f on
-//    [L, U] and its zero is a new upper bound U.
-//  * Tangent of 1/(x + ab) at U: it lies below the function everywhere, so
-//    the same construction gives a function above f and a new lower bound L.
-//  * A second chord over the narrowed [L, U] gives the start (PAIRS such
-//    tangent-and-chord pairs after the first chord).
-// Each bound is the positive zero of (1 + w) x^2 - c x - b1^2, w the line's
-// slope times -b2^2.  The constants c = gb + b2^2 * (the line's value at 0)
-// are written as c0 + b2^2 ((value at 0) - 1/ab), with c0 = gb + b2^2/ab
-// formed in FP64: for a zero small next to |gb| the terms of c0 nearly
-// cancel, while the differences, -L U / ((L + ab)(U + ab) ab) for a chord
-// and -t^2 / ((t + ab)^2 ab) for the tangent at t, are accurate in FP32.
-// In a CPU emulation this start leaves no zero needing three evaluations of
-// f on the SPD and normal workloads (the two chords over [0, U] of bg_start:
-// about 1%), and the FP32 arithmetic costs less than the trips it saves.
-// It is used when the arrow is well inside FP32's normal range (the squares
-// b^2 and a zero b1^2/|gb| that a tiny b1 gives stay normal, b2^2/ab stays
-// finite); otherwise the FP64 bounds of bg_start.  The start may fall on
-// either side of the zero by FP32 rounding; the step handles both.
-// rab = 1/ab.
-template <int PAIRS>
-__device__ __forceinline__ double start_point(const Arrow1& P, double rab) {
-  const Arrow1f Q{(float)P.b1s, (float)P.b2s, (float)P.ab, (float)P.gb};
-  const bool ok = Q.b1s >= 0x1p-120f && Q.b2s >= 0x1p-120f && Q.ab >= 0x1p-100f;
-  const float c0 = (float)__builtin_fma(P.b2s, rab, P.gb);
-  const float rabf = __builtin_amdgcn_rcpf(Q.ab);
-  float L = quad_zero32_1(Q.gb, Q.b1s);
-  float U = quad_zero32_1(Q.gb, Q.b1s + Q.b2s);
-  float rl = __builtin_amdgcn_rcpf(L + Q.ab);
-  float ru = __builtin_amdgcn_rcpf(U + Q.ab);
-  float w = Q.b2s * rl * ru;
-  U = __builtin_fminf(U, quad_zero32(c0 - w * (L * U) * rabf, Q.b1s, 1.0f + w));
-#pragma unroll
-  for (int j = 0; j < PAIRS; ++j) {
-    ru = __builtin_amdgcn_rcpf(U + Q.ab);
-    w = Q.b2s * ru * ru;
-    L = __builtin_fmaxf(L, quad_zero32(c0 - w * (U * U) * rabf, Q.b1s, 1.0f + w));
-    rl = __builtin_amdgcn_rcpf(L + Q.ab);
-    w = Q.b2s * rl * ru;
-    U = __builtin_fminf(U, quad_zero32(c0 - w * (L * U) * rabf, Q.b1s, 1.0f + w));
-  }
-  if (ok && U >= 0x1p-124f && U < 0x1p100f) return (double)U;
-  return bg_start(P, rab);
+// One Borges-Gragg iterate from t (Sec. 1.4.1), as the positive zero of the
+// model itself.  The model takes 1/(x + ab) as A - B x + C/x with the value
+// and first two derivatives matched at t, with p = t + ab:
+//   A = ab (3t + ab)/p^3,  B = ab/p^3,  C = t^3/p^3,
+// so its zero is that of (1 + b2^2 B) x^2 - (gb + b2^2 A) x - (b1^2 + b2^2 C),
+// and gb + b2^2 A = c0 - b2^2 t^2 (t + 3 ab)/(ab p^3).  In this form the
+// iterate needs neither f nor an increment: no cancellation next to the pole
+// at 0, no case for large steps, and every factor formed below (t/p, ab/p
+// <= 1) stays in range.
+__device__ __forceinline__ float bg_iterate32(const Arrow1f& P, float t) {
+  const float r = __builtin_amdgcn_rcpf(t + P.ab);
+  const float g = P.b2s * r, u = t * r;
+  const float w = (g * u) * u;  // b2^2 t^2 / p^3
+  const float a = __builtin_fmaf(g * r, P.ab * r, 1.0f);
+  const float k = __builtin_fmaf(w, t, P.b1s);
+  const float c = __builtin_fmaf(-(w * P.rab), __builtin_fmaf(3.0f, P.ab, t), P.c0);
+  return quad_zero32(c, k, a);
 }
 
-// Tangent-and-chord pairs of the two starts (mu, nu).
-constexpr int kStartPairsMu = 1;
-constexpr int kStartPairsNu = 2;
+// Start of the FP64 zero finder: x_inf (the first iterate from +infinity),
+// one chord over [0, x_inf], and two Borges-Gragg iterates, all in FP32.
+// The chord's zero is close whether the root lies next to the pole at 0 or
+// far from it, so two cubic iterates reach FP32's accuracy: in a CPU
+// emulation of this arithmetic the relative error r stays below 2^-17 for
+// all lanes of 99% of wavefronts on N(0,1), uniform and condition-1e8 SPD
+// matrices and 94-97% on chi-square ones; with x_inf, three chords and one
+// iterate, in 54-99%; without the chord, in at most 92% and mostly none.
+// Nothing is checked here: an arrow that FP32 cannot represent gives some
+// useless value (or NaN), which the FP64 step's test of its correction
+// rejects.
+__device__ __forceinline__ float start_point(const Arrow1f& P) {
+  float x = quad_zero32_1(P.gb, P.b1s + P.b2s);
+  const float k = (P.b2s * P.rab) * __builtin_amdgcn_rcpf(x + P.ab);
+  x = quad_zero32(P.c0, P.b1s, 1.0f + k);
+  x = bg_iterate32(P, x);
+  return bg_iterate32(P, x);
+}
 
+// One FP64 step from x by Chebyshev's third-order correction of Newton's
+// step, x - (f/f')(1 + f f''/(2 f'^2)).  f is evaluated to about one ulp of
+// its terms; the correction itself is small next to x, so one v_rcp_f64 of
+// f' will do: its error e = 1 - f' r is folded in with the second-order
+// term (f'' = -2g).
+//  * done: a correction of at most 2^-17 x.  As t |f''(t)| <= 2 f'(t), a
+//    correction of r x puts the zero within about r x of x, whatever x > 0
+//    was given.  With A2 = g/f' and A3 a sixth of the third derivative over
+//    f', the step leaves |2 A2^2 - A3| times the cube of that distance, at
+//    most r^3 x since x A2 <= 1 and (x A2)^2 <= x^2 A3 <= x A2: 2^-51 x, the
+//    2 eps that bg_update's stop test asks for.  NaN, zero, negative and
+//    infinite x fail it.
+__device__ __forceinline__ double chebyshev_step(const Arrow1& P, double x, bool& done) {
+  const Spec s = spec_eval(P, x);
+  const double g = __builtin_fma(s.q1 * s.rx, s.rx, (s.q2 * s.rp) * s.rp);
+  const double r = __builtin_amdgcn_rcp(s.fp);
+  const double d0 = s.f * r;
+  const double e = __builtin_fma(-s.fp, r, 1.0);
+  const double dx = __builtin_fma(d0, __builtin_fma(-d0, g * r, e), d0);
+  done = dabs(dx) <= 0x1p-17 * x;
+  return x - dx;
+}
 
 // One Borges-Gragg step from x on either side of the zero (Sec. 1.4.1: the
 // iteration converges monotonically from any start in (0, inf)).  Sets stop
@@ -479,20 +481,37 @@ __device__ __forceinline__ double newton_step(const Arrow1& P, double x, bool& s
   return xn;
 }
 
-// Both zeros (mu and nu) in one loop: the two recurrences are independent,
-// so their latencies overlap; the loop runs until both have stopped.
-__device__ __forceinline__ void zeros_bg(const Arrow1& P1, const Arrow1& P2,
+// Both zeros (mu and nu): their FP32 starts, one Chebyshev step each, and
+// Borges-Gragg steps in FP64 on the roots that are not done then (or on all
+// of them: converge).  Those go on from the Chebyshev iterate where it moved
+// by less than a quarter of x, else from the FP64 bounds of bg_start: the
+// arrow was outside FP32's range, or its zero below FP32's resolution.
+// The two recurrences are independent, so their latencies overlap; the loop
+// runs until both have stopped.  It is a branch of its own, which the empty
+// asm keeps from being evaluated on every lane.
+__device__ __forceinline__ void zeros_bg(const Arrow1& P1, const Arrow1& P2, bool converge,
                                          double& x1, double& x2, int& it1, int& it2) {
   const double rab = rcp1(P1.ab);  // both problems share abar
-  x1 = start_point<kStartPairsMu>(P1, rab);
-  x2 = start_point<kStartPairsNu>(P2, rab);
-  bool s1 = false, s2 = false;
-  it1 = 0;
-  it2 = 0;
-  for (int k = 0; k < kMaxIter; ++k) {
-    if (s1 && s2) break;
-    if (!s1) { ++it1; x1 = bg_step(P1, x1, s1); }
-    if (!s2) { ++it2; x2 = bg_step(P2, x2, s2); }
+  const double y1 = (double)start_point(to_f32(P1, rab));
+  const double y2 = (double)start_point(to_f32(P2, rab));
+  bool s1, s2;
+  x1 = chebyshev_step(P1, y1, s1);
+  x2 = chebyshev_step(P2, y2, s2);
+  it1 = 1;
+  it2 = 1;
+  if (converge) {
+    asm volatile("");
+    s1 = s2 = false;
+  }
+  if (!(s1 && s2)) {
+    asm volatile("");
+    if (!s1 && !(dabs(x1 - y1) <= 0.25 * y1)) x1 = bg_start(P1, rab);
+    if (!s2 && !(dabs(x2 - y2) <= 0.25 * y2)) x2 = bg_start(P2, rab);
+    for (int k = 0; k < kMaxIter; ++k) {
+      if (s1 && s2) break;
+      if (!s1) { ++it1; x1 = bg_step(P1, x1, s1); }
+      if (!s2) { ++it2; x2 = bg_step(P2, x2, s2); }
+    }
   }
 }
 
@@ -581,39 +600,6 @@ __device__ __forceinline__ float bg_step32(const Arrow1f& P, float x, bool& stop
     conv = true;
   }
   return m.xn;
-}
-
-// One step from an upper bound of the zero with no stop test, for the start
-// of the FP32-storage form's Newton step (which checks what it is given); a
-// step that does not give a positive iterate leaves x as it is.
-__device__ __forceinline__ float bg_once32(const Arrow1f& P, float x) {
-  const float xn = bg_move32(P, x).xn;
-  return xn > 0.0f ? xn : x;
-}
-
-// One FP64 Newton step on f from an FP32 estimate x of the zero (the
-// iteration of Sec. 1.4.2, as a refinement).  f is increasing and concave
-// with t |f''(t)| <= 2 f'(t), so from a start delta away from the zero, on
-// either side, the step lands left of it by at most about delta^2 / x.
-//  * bad: a correction above 2^-14 x (or a non-positive iterate); the lane
-//    then goes on with FP64 Borges-Gragg steps.  Below it the step leaves
-//    at most about 2^-28 x: as the zero is at most 2 ||A||, an eigenvalue
-//    off by at most eps32 ||A|| / 16 before rounding.
-//  * again: a correction above 2^-22 x; one more step then leaves at most
-//    about 2^-56 x.  An eigenvalue formed as a difference (alpha2 - nu, say)
-//    can be far smaller than the zero, and its relative error is the
-//    zero's error over it: on SPD matrices of condition 1e8, a CPU
-//    emulation of this arithmetic puts the smallest eigenvalue's worst
-//    relative error at 3e-3 after one step and 1e-6 with the second step
-//    where the first moved more than 2^-22 x.
-__device__ __forceinline__ double newton_refine(const Arrow1& P, double x, bool& bad,
-                                                bool& again) {
-  const Spec s = spec_eval(P, x);
-  const double dx = ddiv(s.f, s.fp);
-  const double xn = x - dx;
-  bad = !(dabs(dx) <= 0x1p-14 * x) || !(xn > 0.0);
-  again = !(dabs(dx) <= 0x1p-22 * x);
-  return xn;
 }
 
 // ---------------------------------------------------------------------------
@@ -789,74 +775,11 @@ __device__ __forceinline__ int solve3(const double (&ain)[6], uint32_t flags,
     const Arrow1 P1{b1s, b2s, al, ga - al1};
     const Arrow1 P2{b2s, b1s, al, al2 - ga};
     double mu = 0.0, nu = 0.0;
-    if (FORM == kFormF32R) {
-      // FP32 storage with FP64 refinement: in FP32, the three-chord upper
-      // bound of the zero and one Borges-Gragg step from it; then an FP64
-      // Newton step (Sec. 1.4.2), which squares the relative error, and a
-      // second one where the first moved the zero by more than 2^-22.
-      const double rab = rcp1(P1.ab);  // both problems share abar
-      const Arrow1f Q1{(float)P1.b1s, (float)P1.b2s, (float)P1.ab, (float)P1.gb,
-                       (float)__builtin_fma(P1.b2s, rab, P1.gb), (float)rab};
-      const Arrow1f Q2{(float)P2.b1s, (float)P2.b2s, (float)P2.ab, (float)P2.gb,
-                       (float)__builtin_fma(P2.b2s, rab, P2.gb), (float)rab};
-      const float y1 = bg_once32(Q1, bg_start32<kChordsRefine>(Q1));
-      const float y2 = bg_once32(Q2, bg_start32<kChordsRefine>(Q2));
-      double x1 = (double)y1, x2 = (double)y2;
-      // the FP32 problem must be representable away from the poles
-      if (!(Q1.b1s >= 0x1p-100f && Q1.b2s >= 0x1p-100f && Q1.ab >= 0x1p-60f &&
-            y1 > 0x1p-100f && y2 > 0x1p-100f)) {
-        // no usable FP32 start: the FP64 bounds of bg_start, too far for
-        // the Newton step, whose check then hands them to FP64 Borges-Gragg
-        // (a branch of its own, which the empty asm keeps from being
-        // evaluated on every lane)
-        asm volatile("");
-        x1 = bg_start(P1, rab);
-        x2 = bg_start(P2, rab);
-      }
-      bool bad1, bad2, again1, again2, unused;
-      mu = newton_refine(P1, x1, bad1, again1);
-      nu = newton_refine(P2, x2, bad2, again2);
-      it1 = it2 = 2;  // one FP32 and one FP64 evaluation of f per root
-      if (flags & kFlagRefineConverge) bad1 = bad2 = true;
-      // the second Newton step, per root, where the first moved the zero by
-      // more than 2^-22 of it (and the lane is not going on to Borges-Gragg);
-      // branches of their own (the empty asm keeps the compiler from
-      // evaluating them on every lane), skipped by wavefronts none of whose
-      // lanes need them
-      if (again1 && !bad1) {
-        asm volatile("");
-        ++it1;
-        mu = newton_refine(P1, mu, unused, unused);
-      }
-      if (again2 && !bad2) {
-        asm volatile("");
-        ++it2;
-        nu = newton_refine(P2, nu, unused, unused);
-      }
-      if (bad1 || bad2) {
-        // The start was too far for one Newton step (a zero FP32 does not
-        // resolve, or an arrow outside FP32's range), or every root
-        // converges (kFlagRefineConverge): continue with FP64 Borges-Gragg
-        // steps.  f is concave, so the Newton iterate lies left of the zero
-        // when the start is right of it; when it is not positive the start
-        // is taken instead.
-        if (bad1 && !(mu > 0.0)) mu = x1;
-        if (bad2 && !(nu > 0.0)) nu = x2;
-        bool s1 = !bad1, s2 = !bad2;
-        for (int k = 0; k < kMaxIter; ++k) {
-          if (s1 && s2) break;
-          if (!s1) { ++it1; mu = bg_step(P1, mu, s1); }
-          if (!s2) { ++it2; nu = bg_step(P2, nu, s2); }
-        }
-      }
-    } else if (FORM == kFormF32) {
+    if (FORM == kFormF32) {
       // The unrefined FP32 ablation: Borges-Gragg in FP32 from the FP32
       // two-chord start, its zeros used as they are.
       const double rab = rcp1(P1.ab);  // both problems share abar
-      const Arrow1f Q1{(float)P1.b1s, (float)P1.b2s, (float)P1.ab, (float)P1.gb,
-                       (float)__builtin_fma(P1.b2s, rab, P1.gb), (float)rab};
-      const Arrow1f Q2{(float)P2.b1s, (float)P2.b2s, (float)P2.ab, (float)P2.gb,
-                       (float)__builtin_fma(P2.b2s, rab, P2.gb), (float)rab};
+      const Arrow1f Q1 = to_f32(P1, rab), Q2 = to_f32(P2, rab);
       // the FP32 problem must be representable away from the poles
       bool fb = !(Q1.b1s >= 0x1p-100f && Q1.b2s >= 0x1p-100f && Q1.ab >= 0x1p-60f);
       float y1 = bg_start32<kChords>(Q1), y2 = bg_start32<kChords>(Q2);
@@ -870,19 +793,23 @@ __device__ __forceinline__ int solve3(const double (&ain)[6], uint32_t flags,
       if (fb) {
         // no usable FP32 zero: the FP64 zero finder from its own start
         int j1, j2;
-        zeros_bg(P1, P2, mu, nu, j1, j2);
+        zeros_bg(P1, P2, false, mu, nu, j1, j2);
         it1 += j1;
         it2 += j2;
       } else {
         mu = (double)y1;
         nu = (double)y2;
       }
+    } else if (FORM == kFormF32R) {
+      zeros_bg(P1, P2, flags & kFlagRefineConverge, mu, nu, it1, it2);
+      it1 += 2;  // and the two FP32 iterates of the start
+      it2 += 2;
     } else if (flags & kFlagNewton) {
       zeros_newton(P1, P2, mu, nu, it1, it2);
     } else if (flags & kFlagPaperBG) {
       zeros_bg_paper(P1, P2, mu, nu, it1, it2);
     } else {
-      zeros_bg(P1, P2, mu, nu, it1, it2);
+      zeros_bg(P1, P2, false, mu, nu, it1, it2);
     }
     // lambda3 <= lambda2 <= lambda1; lambda2 by the trace identity
     l2 = al1 + mu;
