@@ -9,7 +9,8 @@
 //     read with unit-stride lanes (16 bytes each) into LDS and each lane then
 //     picks up its own 6 entries (the transpose).  Outputs go back through
 //     LDS the same way, so global stores are unit-stride as well.
-// Streams are read and written once, with non-temporal hints (no reuse).
+// Streams are read and written once; how (workgroup order, non-temporal
+// hints, workgroups per compute unit) is chosen per launch, in motion().
 #include <type_traits>
 
 #include "syev3_internal.hpp"
@@ -19,34 +20,37 @@ namespace syev3 {
 
 // Workgroup order.  The dispatcher deals workgroups to the 8 XCDs in turn,
 // so in launch order neighbouring tiles of the batch run on different XCDs.
-// For large batches each XCD instead takes kXcdChunk consecutive tiles at a
-// time (the blocks of a partial last round of 8 * kXcdChunk keep their own
-// index; any bijection is correct).  Measured on FP64 SoA solves of N(0,1)
-// matrices: launch order falls from 5.7 TB/s at 2^25 matrices to 5.1-5.3
-// TB/s at 2^26-2^28, chunks of 256 tiles (64K matrices, 512 KB of each FP64
-// plane) hold 5.4-5.8 TB/s there (+9% at 2^26); at 2^24 launch order is as
-// good or better; 64-tile chunks are slower than launch order, 512-1024
-// close to 256.  The pure streaming reference is fastest in launch order,
-// so it keeps it.
+// In the chunked order each XCD instead takes 2^log2_chunk consecutive tiles
+// at a time, over the first `chunked` workgroups (a multiple of 8 chunks, or
+// 0 for launch order); the rest keep their own index.
 constexpr uint32_t kXcds = 8;
 constexpr int kWave = 64;  // gfx950 runs wave64
-constexpr uint32_t kXcdChunk = 256;
-constexpr uint32_t kChunkFromBlocks = 1u << 17;  // 2^25 matrices
 
-__device__ __forceinline__ uint32_t tile_of_block(uint32_t b, uint32_t nb) {
-  constexpr uint32_t G = kXcds * kXcdChunk;
-  if (nb < kChunkFromBlocks || b >= nb / G * G) return b;
+struct Order {
+  uint32_t chunked, log2_chunk;
+};
+
+__device__ __forceinline__ uint32_t tile_of_block(uint32_t b, Order o) {
+  if (b >= o.chunked) return b;
   const uint32_t x = b % kXcds, slot = b / kXcds;
-  return slot / kXcdChunk * G + x * kXcdChunk + slot % kXcdChunk;
+  const uint32_t in = slot & ((1u << o.log2_chunk) - 1);
+  return (((slot >> o.log2_chunk) * kXcds + x) << o.log2_chunk) + in;
 }
 
-template <typename T>
-__device__ __forceinline__ T ld_stream(const T* p) {
-  return __builtin_nontemporal_load(p);
+inline Order chunked_order(int64_t blocks, uint32_t log2_chunk) {
+  const int64_t round = (int64_t)kXcds << log2_chunk;
+  return Order{(uint32_t)(blocks / round * round), log2_chunk};
 }
-template <typename T>
-__device__ __forceinline__ void st_stream(T v, T* p) {
-  __builtin_nontemporal_store(v, p);
+
+// NT: with the non-temporal hint.
+template <bool NT, typename T>
+__device__ __forceinline__ T ld(const T* p) {
+  return NT ? __builtin_nontemporal_load(p) : *p;
+}
+template <bool NT, typename T>
+__device__ __forceinline__ void st(T v, T* p) {
+  if (NT) __builtin_nontemporal_store(v, p);
+  else *p = v;
 }
 
 // The element type a form stores: double for FP64, float for both FP32
@@ -71,30 +75,31 @@ struct Planes {
 
 // T = double: FP64 path.  T = float: FP32 storage with FP64 refinement.
 // 64-bit element offsets, for planes of more than 2^32 bytes.
-template <int FORM, bool VECS, bool INFO>
+template <int FORM, bool VECS, bool INFO, bool NT>
 __global__ __launch_bounds__(kBlock) void k_syev3_soa(int64_t n, Planes<Storage<FORM>> P,
-                                                     uint32_t flags, int32_t* __restrict__ info) {
+                                                     uint32_t flags, Order order,
+                                                     int32_t* __restrict__ info) {
   using T = Storage<FORM>;
-  const int64_t i = (int64_t)tile_of_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
+  const int64_t i = (int64_t)tile_of_block(blockIdx.x, order) * kBlock + threadIdx.x;
   if (i >= n) return;
   double a[6];
 #pragma unroll
-  for (int k = 0; k < 6; ++k) a[k] = (double)ld_stream(P.a[k] + i);
+  for (int k = 0; k < 6; ++k) a[k] = (double)ld<NT>(P.a[k] + i);
   double l[3], v[9];
   bool bad;
   const int code = solve3<VECS, FORM>(a, flags, l, v, bad);
 #pragma unroll
-  for (int j = 0; j < 3; ++j) st_stream((T)l[j], P.l[j] + i);
+  for (int j = 0; j < 3; ++j) st<NT>((T)l[j], P.l[j] + i);
   if (VECS) {
 #pragma unroll
-    for (int k = 0; k < 9; ++k) st_stream((T)v[k], P.v[k] + i);
+    for (int k = 0; k < 9; ++k) st<NT>((T)v[k], P.v[k] + i);
   }
   if (bad) {  // a NaN or infinite entry: NaN in every output of the matrix
 #pragma unroll
-    for (int j = 0; j < 3; ++j) st_stream(qnan<T>(), P.l[j] + i);
+    for (int j = 0; j < 3; ++j) st<NT>(qnan<T>(), P.l[j] + i);
     if (VECS) {
 #pragma unroll
-      for (int k = 0; k < 9; ++k) st_stream(qnan<T>(), P.v[k] + i);
+      for (int k = 0; k < 9; ++k) st<NT>(qnan<T>(), P.v[k] + i);
     }
   }
   if (INFO) info[i] = code;
@@ -104,17 +109,18 @@ __global__ __launch_bounds__(kBlock) void k_syev3_soa(int64_t n, Planes<Storage<
 // loads and stores take the scalar-base addressing form and need no 64-bit
 // address arithmetic per lane.
 
-template <int FORM, bool VECS, bool INFO>
+template <int FORM, bool VECS, bool INFO, bool NT>
 __global__ __launch_bounds__(kBlock) void k_syev3_soa32(uint32_t n, Planes<Storage<FORM>> P,
-                                                       uint32_t flags, int32_t* __restrict__ info) {
+                                                       uint32_t flags, Order order,
+                                                       int32_t* __restrict__ info) {
   using T = Storage<FORM>;
-  const uint32_t i = tile_of_block(blockIdx.x, gridDim.x) * (uint32_t)kBlock + threadIdx.x;
+  const uint32_t i = tile_of_block(blockIdx.x, order) * (uint32_t)kBlock + threadIdx.x;
   if (i >= n) return;
   const uint32_t off = i * (uint32_t)sizeof(T);  // byte offset within a plane
   double a[6];
 #pragma unroll
   for (int k = 0; k < 6; ++k)
-    a[k] = (double)ld_stream((const T*)((const char*)P.a[k] + off));
+    a[k] = (double)ld<NT>((const T*)((const char*)P.a[k] + off));
   double l[3], v[9];
   bool bad;
   const int code = solve3<VECS, FORM>(a, flags, l, v, bad);
@@ -125,17 +131,17 @@ __global__ __launch_bounds__(kBlock) void k_syev3_soa32(uint32_t n, Planes<Stora
   uint32_t soff = off;
   asm volatile("" : "+v"(soff));
 #pragma unroll
-  for (int j = 0; j < 3; ++j) st_stream((T)l[j], (T*)((char*)P.l[j] + soff));
+  for (int j = 0; j < 3; ++j) st<NT>((T)l[j], (T*)((char*)P.l[j] + soff));
   if (VECS) {
 #pragma unroll
-    for (int k = 0; k < 9; ++k) st_stream((T)v[k], (T*)((char*)P.v[k] + soff));
+    for (int k = 0; k < 9; ++k) st<NT>((T)v[k], (T*)((char*)P.v[k] + soff));
   }
   if (bad) {  // a NaN or infinite entry: NaN in every output of the matrix
 #pragma unroll
-    for (int j = 0; j < 3; ++j) st_stream(qnan<T>(), (T*)((char*)P.l[j] + soff));
+    for (int j = 0; j < 3; ++j) st<NT>(qnan<T>(), (T*)((char*)P.l[j] + soff));
     if (VECS) {
 #pragma unroll
-      for (int k = 0; k < 9; ++k) st_stream(qnan<T>(), (T*)((char*)P.v[k] + soff));
+      for (int k = 0; k < 9; ++k) st<NT>(qnan<T>(), (T*)((char*)P.v[k] + soff));
     }
   }
   if (INFO) info[i] = code;
@@ -153,10 +159,10 @@ __device__ __forceinline__ void copy_in(T* sm, const T* g, int total, int t) {
   int k0 = 0;
   if (((uintptr_t)g & 15u) == 0) {
     const int nv = total / W;
-    for (int k = t; k < nv; k += kBlock) ((vec*)sm)[k] = ld_stream((const vec*)g + k);
+    for (int k = t; k < nv; k += kBlock) ((vec*)sm)[k] = ld<true>((const vec*)g + k);
     k0 = nv * W;
   }
-  for (int k = k0 + t; k < total; k += kBlock) sm[k] = ld_stream(g + k);
+  for (int k = k0 + t; k < total; k += kBlock) sm[k] = ld<true>(g + k);
 }
 
 // The same for a full tile, whose size is known at compile time: every lane
@@ -174,7 +180,7 @@ __device__ __forceinline__ void copy_in_full(T* sm, const T* g, int t) {
 #pragma unroll
   for (int j = 0; j < R; ++j) {
     const int k = t + j * kBlock;
-    if (j + 1 < R || k < NV) x[j] = ld_stream((const vec*)g + k);
+    if (j + 1 < R || k < NV) x[j] = ld<true>((const vec*)g + k);
   }
 #pragma unroll
   for (int j = 0; j < R; ++j) {
@@ -199,7 +205,7 @@ __device__ __forceinline__ void copy_out_full(T* g, const T* sm, int t) {
 #pragma unroll
   for (int j = 0; j < R; ++j) {
     const int k = t + j * kBlock;
-    if (j + 1 < R || k < NV) st_stream(x[j], (vec*)g + k);
+    if (j + 1 < R || k < NV) st<true>(x[j], (vec*)g + k);
   }
 }
 
@@ -210,11 +216,14 @@ __device__ __forceinline__ void copy_out(T* g, const T* sm, int total, int t) {
   int k0 = 0;
   if (((uintptr_t)g & 15u) == 0) {
     const int nv = total / W;
-    for (int k = t; k < nv; k += kBlock) st_stream(((const vec*)sm)[k], (vec*)g + k);
+    for (int k = t; k < nv; k += kBlock) st<true>(((const vec*)sm)[k], (vec*)g + k);
     k0 = nv * W;
   }
-  for (int k = k0 + t; k < total; k += kBlock) st_stream(sm[k], g + k);
+  for (int k = k0 + t; k < total; k += kBlock) st<true>(sm[k], g + k);
 }
+
+template <typename T>
+constexpr size_t kAosLds = kBlock * 9 * sizeof(T);
 
 // AoS: IN = 6 (unique entries) or 9 (full row-major matrix, upper triangle
 // read).  The whole block is read into LDS before any global store, so the
@@ -226,10 +235,10 @@ __device__ __forceinline__ void copy_out(T* g, const T* sm, int total, int t) {
 template <int FORM, int IN, bool VECS, bool INFO>
 __global__ __launch_bounds__(kBlock) void k_syev3_aos(
     int64_t n, const Storage<FORM>* A, Storage<FORM>* __restrict__ lam, Storage<FORM>* V,
-    uint32_t flags, int32_t* __restrict__ info) {
+    uint32_t flags, Order order, int32_t* __restrict__ info) {
   using T = Storage<FORM>;
-  __shared__ __attribute__((aligned(16))) T sm[kBlock * 9];
-  const int64_t base = (int64_t)tile_of_block(blockIdx.x, gridDim.x) * kBlock;
+  __shared__ __attribute__((aligned(16))) T sm[kAosLds<T> / sizeof(T)];
+  const int64_t base = (int64_t)tile_of_block(blockIdx.x, order) * kBlock;
   const int cnt = (int)((n - base) < kBlock ? (n - base) : kBlock);
   const int t = threadIdx.x;
   const T* Ab = A + base * IN;
@@ -283,6 +292,96 @@ __global__ __launch_bounds__(kBlock) void k_syev3_aos(
   }
 }
 
+// How a launch moves its data: the workgroup order, the non-temporal hints,
+// and dynamic LDS the kernel does not use, which caps the workgroups a
+// compute unit holds.
+struct Motion {
+  Order order;
+  bool nt;
+  size_t lds;
+};
+
+// LDS of a workgroup that lets 3 of them (12 wavefronts) onto a compute unit
+// (160 KB) instead of the 8 that the registers allow.
+constexpr size_t kLdsFor3 = 52 << 10;
+// From here (786K matrices, 12 workgroups per compute unit) the cap's extra
+// rounds are many enough not to leave compute units idle in the last one.
+constexpr int64_t kManyBlocks = 3072;
+
+// The rules, each with both sides measured (us; three sets of buffers in
+// turn, N(0,1) matrices):
+//  * FP64 with vectors, bound by HBM, caps its workgroups at 3 per compute
+//    unit from kManyBlocks on: fewer wavefronts mix fewer reads into the
+//    writes, and 12 per compute unit still cover the solve.  SoA 2^24 393
+//    (cap) against 426, 60 M 1458 against 1602; AoS 2^24 390 against 445.
+//    Below, the cap costs whole rounds (400,000: 13.2 against 10.4).
+//    Eigenvalues only and FP32 storage (72 bytes or less per matrix) need
+//    the wavefronts: FP32 vectors 2^24 212 without the cap, 286 with it.
+//  * SoA planes that do not all start on a 128-byte line (any odd n, for
+//    one): neighbouring wavefronts, and at a tile's edge neighbouring
+//    workgroups, share lines.  Non-temporal stores then write partial lines
+//    to memory, so loads and stores go through L2 as usual, and chunks of 32
+//    tiles keep neighbours on one XCD's L2: FP64 16,777,293 matrices 435
+//    against 607 with the hints in launch order (487 without either), 60 M
+//    1592 against 2154; FP32 30 M 430 against 585.  Three planes of
+//    eigenvalues alone lose little to it and keep the hints (FP64 30 M 380
+//    against 384), as does FP32 storage below kManyBlocks (500,003: 9.6
+//    against 10.2).
+//  * FP64 vectors below kManyBlocks take the plain accesses for any planes:
+//    inputs and results of such a batch stay in the caches (400,000: 10.4
+//    against 14.8).  The chunked order pays from 1280 blocks (400,000: 10.4
+//    against 11.5; 300,001: 9.0 against 8.7).
+//  * Otherwise the hints: FP64 vectors 2^24 393 against 406 without.  The
+//    order is launch order (60 M: 1458, in chunks of 256 tiles 1569), but
+//    for AoS chunks of 32 (2^24: 390 against 399; 60 M: 1406 against 1475)
+//    and, where the plane stride comes within 64 KB of a multiple of 2^29
+//    bytes, so that all planes meet the same channels at once, chunks of
+//    256 (2^26 + 4096: 1677 against 1837; 2^27: 3424 against 3543; 2^26:
+//    1626 against 1751 on one device, 1674 against 1670 on another).
+template <int FORM, bool VECS>
+static Motion motion(int64_t blocks, const void* A, Strides ld, int layout, const void* lambda,
+                     const void* V, uint32_t flags) {
+  using T = Storage<FORM>;
+  constexpr bool kHbmBound = FORM == kFormF64 && VECS;
+  const Order launch{0, 0};
+  // the slower zero finders are bound by VALU and need the wavefronts
+  const bool valu = flags & (kFlagNewton | kFlagPaperBG);
+  const bool many = blocks >= kManyBlocks;
+  if (layout != 0) {
+    if (kHbmBound && many) return Motion{chunked_order(blocks, 5), true,
+                                              valu ? 0 : kLdsFor3 - kAosLds<T>};
+    return Motion{launch, true, 0};
+  }
+  if (!VECS) return Motion{launch, true, 0};
+  const uintptr_t bits = (uintptr_t)A | (uintptr_t)lambda | (uintptr_t)V |
+                         (uintptr_t)(ld.a | ld.l | ld.v) * sizeof(T);
+  const bool ragged = (bits & 127u) != 0;
+  if (kHbmBound ? ragged || !many : ragged && many)
+    return Motion{blocks >= 1280 ? chunked_order(blocks, 5) : launch, false,
+                  kHbmBound && many && !valu ? kLdsFor3 : 0};
+  if (!kHbmBound) return Motion{launch, true, 0};
+  const uint64_t off = ((uint64_t)ld.v * sizeof(T) + (1u << 16)) & ((1u << 29) - 1);
+  return Motion{off <= (1u << 17) ? chunked_order(blocks, 8) : launch, true,
+                valu ? 0 : kLdsFor3};
+}
+
+template <int FORM, bool VECS, bool INFO, bool NT>
+static void launch_soa(int64_t n, const void* A, Strides ld, void* lambda, void* V,
+                       uint32_t flags, const Motion& m, int32_t* info, dim3 grid, dim3 block,
+                       hipStream_t stream) {
+  using T = Storage<FORM>;
+  Planes<T> P;
+  for (int k = 0; k < 6; ++k) P.a[k] = (const T*)A + k * ld.a;
+  for (int j = 0; j < 3; ++j) P.l[j] = (T*)lambda + j * ld.l;
+  for (int k = 0; k < 9; ++k) P.v[k] = VECS ? (T*)V + k * ld.v : nullptr;
+  if ((uint64_t)n * sizeof(T) <= (uint64_t)UINT32_MAX)
+    hipLaunchKernelGGL((k_syev3_soa32<FORM, VECS, INFO, NT>), grid, block, m.lds, stream,
+                       (uint32_t)n, P, flags, m.order, info);
+  else
+    hipLaunchKernelGGL((k_syev3_soa<FORM, VECS, INFO, NT>), grid, block, m.lds, stream, n, P,
+                       flags, m.order, info);
+}
+
 template <int FORM, bool VECS, bool INFO>
 static hipError_t launch_t(int64_t n, const void* A, Strides ld, int layout,
                            void* lambda, void* V, uint32_t flags, int32_t* info,
@@ -290,23 +389,21 @@ static hipError_t launch_t(int64_t n, const void* A, Strides ld, int layout,
   using T = Storage<FORM>;
   const int64_t blocks = (n + kBlock - 1) / kBlock;
   const dim3 grid((unsigned)blocks), block(kBlock);
+  const Motion m = motion<FORM, VECS>(blocks, A, ld, layout, lambda, V, flags);
   if (layout == 0) {
-    Planes<T> P;
-    for (int k = 0; k < 6; ++k) P.a[k] = (const T*)A + k * ld.a;
-    for (int j = 0; j < 3; ++j) P.l[j] = (T*)lambda + j * ld.l;
-    for (int k = 0; k < 9; ++k) P.v[k] = VECS ? (T*)V + k * ld.v : nullptr;
-    if ((uint64_t)n * sizeof(T) <= (uint64_t)UINT32_MAX)
-      hipLaunchKernelGGL((k_syev3_soa32<FORM, VECS, INFO>), grid, block, 0, stream, (uint32_t)n,
-                         P, flags, info);
+    // eigenvalues alone always take the hints
+    if (m.nt || !VECS)
+      launch_soa<FORM, VECS, INFO, true>(n, A, ld, lambda, V, flags, m, info, grid, block,
+                                         stream);
     else
-      hipLaunchKernelGGL((k_syev3_soa<FORM, VECS, INFO>), grid, block, 0, stream, n, P, flags,
-                         info);
+      launch_soa<FORM, VECS, INFO, !VECS>(n, A, ld, lambda, V, flags, m, info, grid, block,
+                                          stream);
   } else if (layout == 1) {
-    hipLaunchKernelGGL((k_syev3_aos<FORM, 6, VECS, INFO>), grid, block, 0, stream, n,
-                       (const T*)A, (T*)lambda, (T*)V, flags, info);
+    hipLaunchKernelGGL((k_syev3_aos<FORM, 6, VECS, INFO>), grid, block, m.lds, stream, n,
+                       (const T*)A, (T*)lambda, (T*)V, flags, m.order, info);
   } else {
-    hipLaunchKernelGGL((k_syev3_aos<FORM, 9, VECS, INFO>), grid, block, 0, stream, n,
-                       (const T*)A, (T*)lambda, (T*)V, flags, info);
+    hipLaunchKernelGGL((k_syev3_aos<FORM, 9, VECS, INFO>), grid, block, m.lds, stream, n,
+                       (const T*)A, (T*)lambda, (T*)V, flags, m.order, info);
   }
   return hipGetLastError();
 }
@@ -487,21 +584,22 @@ hipError_t launch_segments(const TickTable* table, int32_t grid_blocks,
 template <typename T, bool VECS, bool RD, bool WR, bool XCD>
 __global__ __launch_bounds__(kBlock) void k_stream_reference(int64_t n, const T* __restrict__ A,
                                                              T* __restrict__ lam,
-                                                             T* __restrict__ V) {
-  const uint32_t b = XCD ? tile_of_block(blockIdx.x, gridDim.x) : blockIdx.x;
+                                                             T* __restrict__ V,
+                                                             Order order) {
+  const uint32_t b = XCD ? tile_of_block(blockIdx.x, order) : blockIdx.x;
   const int64_t i = (int64_t)b * kBlock + threadIdx.x;
   if (i >= n) return;
   T s = RD ? (T)0 : (T)threadIdx.x;
   if (RD) {
 #pragma unroll
-    for (int k = 0; k < 6; ++k) s += ld_stream(A + k * n + i);
+    for (int k = 0; k < 6; ++k) s += ld<true>(A + k * n + i);
   }
   if (WR) {
 #pragma unroll
-    for (int j = 0; j < 3; ++j) st_stream(s * (T)(j + 1), lam + j * n + i);
+    for (int j = 0; j < 3; ++j) st<true>(s * (T)(j + 1), lam + j * n + i);
     if (VECS) {
 #pragma unroll
-      for (int k = 0; k < 9; ++k) st_stream(s * (T)(k + 4), V + k * n + i);
+      for (int k = 0; k < 9; ++k) st<true>(s * (T)(k + 4), V + k * n + i);
     }
   } else if (__builtin_isnan(s)) {
     lam[i] = s;
@@ -513,10 +611,11 @@ static hipError_t launch_probe_t(int64_t n, const T* A, T* lambda, T* V, uint32_
                                  hipStream_t stream) {
   const dim3 grid((unsigned)((n + kBlock - 1) / kBlock)), block(kBlock);
   const bool rd = mode & 1u, wr = mode & 2u, xcd = mode & 4u;
+  const Order order = chunked_order(grid.x, 8);
 #define SYEV3_PROBE_CASE(R, W, X)                                                         \
   if (rd == R && wr == W && xcd == X) {                                                   \
     hipLaunchKernelGGL((k_stream_reference<T, VECS, R, W, X>), grid, block, 0, stream, n, \
-                       A, lambda, V);                                                     \
+                       A, lambda, V, order);                                              \
     return hipGetLastError();                                                             \
   }
   SYEV3_PROBE_CASE(true, true, false)

@@ -1,0 +1,62 @@
+"""The dispatch of a batch's data movement (workgroup order, non-temporal or
+plain accesses, workgroups per compute unit) changes no result: around each of
+its limits, for aligned and unaligned planes and in every layout, a batch
+equals, bit for bit, the same matrices solved in small launches, which take
+none of it."""
+import pytest
+import torch
+
+import paper_1806_06698_amd as s3
+from paper_1806_06698_amd import gen
+
+pytestmark = pytest.mark.gpu
+
+BLOCK = 256
+PIECE = 1000 * BLOCK  # below every limit
+
+
+def _pieces(A):
+    """The solution of A (6, n), contiguous pieces solved one by one."""
+    outs = [s3.syev3(A[:, i:i + PIECE].contiguous()) for i in range(0, A.shape[1], PIECE)]
+    return torch.cat([l for l, _ in outs], 1), torch.cat([v for _, v in outs], 1)
+
+
+def _strided(rows, n, ld, first, dtype):
+    """An uninitialised (rows, n) view, row stride ld, `first` elements into
+    its buffer."""
+    return torch.empty(rows * ld + first, dtype=dtype,
+                       device="cuda")[first:].view(rows, ld)[:, :n]
+
+
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32], ids=["f64", "f32"])
+@pytest.mark.parametrize("n", [1280 * BLOCK - 1, 1280 * BLOCK, 1281 * BLOCK + 5,
+                               3071 * BLOCK, 3072 * BLOCK, 3072 * BLOCK + 1,
+                               5000 * BLOCK + 77])
+def test_limits(n, dtype):
+    A, _ = gen.stress_mix(n, 60, "cuda")
+    A = A.to(dtype).contiguous()
+    lam, V = _pieces(A)
+    got = {"default": s3.syev3(A)}
+    # the planes of every array on 128-byte lines, and off them
+    up = (n + 31) // 32 * 32
+    for name, ld, first in (("aligned", up, 0), ("offset", up, 1), ("odd stride", up + 1, 0)):
+        out = (_strided(3, n, ld, first, dtype), _strided(9, n, ld, first, dtype))
+        got[name] = s3.syev3(A, out=out)
+    for name, (l, v) in got.items():
+        assert torch.equal(l, lam) and torch.equal(v, V), name
+    assert torch.equal(s3.syev3(A, vectors=False)[0], lam)
+    la, va = s3.syev3(gen.to_aos(A), layout="aos")
+    assert torch.equal(la.t(), lam) and torch.equal(va.reshape(n, 9).t(), V)
+
+
+def test_planes_half_a_gigabyte_apart():
+    """Plane strides at and within 64 KB of 2^29 bytes (chunks of 256 tiles),
+    and just outside."""
+    n = 4100 * BLOCK + 33
+    A, _ = gen.stress_mix(n, 61, "cuda")
+    lam, V = _pieces(A)
+    for ld in (1 << 26, (1 << 26) - (1 << 13), (1 << 26) + (1 << 13), (1 << 26) + (1 << 14)):
+        l, v = s3.syev3(A, out=(_strided(3, n, ld, 0, A.dtype), _strided(9, n, ld, 0, A.dtype)))
+        assert torch.equal(l, lam) and torch.equal(v, V), ld
+        del l, v
+        torch.cuda.empty_cache()
