@@ -337,7 +337,10 @@ constexpr int64_t kManyBlocks = 3072;
 //    and, where the plane stride comes within 64 KB of a multiple of 2^29
 //    bytes, so that all planes meet the same channels at once, chunks of
 //    256 (2^26 + 4096: 1677 against 1837; 2^27: 3424 against 3543; 2^26:
-//    1626 against 1751 on one device, 1674 against 1670 on another).
+//    1626 against 1751 on one device, 1674 against 1670 on another).  The
+//    unrefined FP32 form does the same at 2^28 bytes (2^26: 908 against 961);
+//    the refined one gains nothing from it (912 against 918; 1014 against
+//    954 on another device).
 template <int FORM, bool VECS>
 static Motion motion(int64_t blocks, const void* A, Strides ld, int layout, const void* lambda,
                      const void* V, uint32_t flags) {
@@ -359,10 +362,11 @@ static Motion motion(int64_t blocks, const void* A, Strides ld, int layout, cons
   if (kHbmBound ? ragged || !many : ragged && many)
     return Motion{blocks >= 1280 ? chunked_order(blocks, 5) : launch, false,
                   kHbmBound && many && !valu ? kLdsFor3 : 0};
-  if (!kHbmBound) return Motion{launch, true, 0};
-  const uint64_t off = ((uint64_t)ld.v * sizeof(T) + (1u << 16)) & ((1u << 29) - 1);
-  return Motion{off <= (1u << 17) ? chunked_order(blocks, 8) : launch, true,
-                valu ? 0 : kLdsFor3};
+  const uint64_t far = kHbmBound ? 1u << 29 : 1u << 28;
+  const uint64_t off = ((uint64_t)ld.v * sizeof(T) + (1u << 16)) & (far - 1);
+  const bool aliased = FORM != kFormF32R && off <= (1u << 17);
+  return Motion{aliased ? chunked_order(blocks, 8) : launch, true,
+                kHbmBound && !valu ? kLdsFor3 : 0};
 }
 
 template <int FORM, bool VECS, bool INFO, bool NT>

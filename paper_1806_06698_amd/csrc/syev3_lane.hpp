@@ -41,7 +41,8 @@ namespace syev3 {
 
 constexpr double kEps64 = 0x1p-52;
 constexpr float kEps32 = 0x1p-23f;
-constexpr int kMaxIter = 32;     // zero-finder evaluations per root (FP64)
+constexpr int kMaxIter = 32;     // Borges-Gragg steps per root (FP64)
+constexpr int kMaxHalley = 4;    // Halley steps before them, after the first
 constexpr int kMaxIter32 = 24;   // FP32 zero-finder evaluations per root
 
 constexpr uint32_t kFlagSimplified = 1u;
@@ -169,7 +170,7 @@ struct Arrow1 {
 // f and f' at x > 0, with b1^2/x and b2^2/(x + ab) to about one ulp from a
 // single reciprocal of x (x + ab).
 struct Spec {
-  double f, fp, rx, rp, q1, q2;
+  double f, fp, rx, rp, q2;
 };
 
 __device__ __forceinline__ Spec spec_eval(const Arrow1& P, double x) {
@@ -183,7 +184,6 @@ __device__ __forceinline__ Spec spec_eval(const Arrow1& P, double x) {
   s.fp = __builtin_fma(q1, rx, __builtin_fma(q2, rp, 1.0));
   s.rx = rx;
   s.rp = rp;
-  s.q1 = q1;
   s.q2 = q2;
   return s;
 }
@@ -229,21 +229,7 @@ __device__ __forceinline__ double bg_start(const Arrow1& P, double rab) {
 
 // FP32 versions (v_rcp_f32 and v_sqrt_f32 are accurate to about one ulp),
 // for the start of the FP64 zero finder and for the FP32 zero finder of the
-// unrefined FP32 ablation.  The start is where single precision pays: an
-// FP32 multiply, add or FMA takes half the issue time of an FP64 one
-// (measured: 2 against 4 cycles per wavefront), v_rcp_f32 and v_sqrt_f32
-// half that of v_rcp_f64 and v_rsq_f64 (8 against 16), and FP64 FMAs lower
-// the clock besides.
-// c0 = gb + b2^2/ab and rab = 1/ab are formed in FP64 and rounded.
-struct Arrow1f {
-  float b1s, b2s, ab, gb, c0, rab;
-};
-
-__device__ __forceinline__ Arrow1f to_f32(const Arrow1& P, double rab) {
-  return Arrow1f{(float)P.b1s, (float)P.b2s, (float)P.ab, (float)P.gb,
-                 (float)__builtin_fma(P.b2s, rab, P.gb), (float)rab};
-}
-
+// unrefined FP32 ablation.
 __device__ __forceinline__ float quad_zero32(float c, float k, float a) {
   const float c2 = 0.5f * c;
   const float s = __builtin_fabsf(c2) + __builtin_amdgcn_sqrtf(__builtin_fmaf(c2, c2, a * k));
@@ -258,80 +244,114 @@ __device__ __forceinline__ float quad_zero32_1(float c, float k) {
   return c >= 0.0f ? s : k * __builtin_amdgcn_rcpf(s);
 }
 
-// The chord bounds of bg_start in FP32 (CHORDS chords); the chords'
-// constant is c0, which FP32 could not form where its terms cancel.
-template <int CHORDS>
+// The numerator of f: F(x) = x (x + ab) f(x) = x^3 + A x^2 - K x - C with
+//   A = ab - gb,  K = ab gb + b1^2 + b2^2 = ab c0 + b1^2,  C = b1^2 ab.
+// F is a shift of the arrow's characteristic polynomial: its zeros are real,
+// the one sought the only positive one.  Every term is formed from A, K and
+// C once, in FP64: K is where the data cancels (c0 = gb + b2^2/ab is the
+// zero's scale next to the pole), and as the start and the step that follows
+// take the same rounded K, they agree on the zero to all its digits, however
+// little of it the cancellation has left.  (f itself, evaluated term by
+// term, moves a zero far below |gb| by its own rounding: FP64 steps on f
+// after a start from c0 needed a second trip in 55% of wavefronts of the
+// stress mix, steps on F in under 1%.)
+struct Cubic {
+  double A, K, C;
+};
+
+__device__ __forceinline__ Cubic cubic(const Arrow1& P, double hh) {
+  return Cubic{P.ab - P.gb, __builtin_fma(P.ab, P.gb, hh), P.b1s * P.ab};
+}
+
+// One step of Laguerre's method on F in FP32, x - 3F / (F' + 2 sqrt(F'^2 -
+// 3 F F''/2)): third order, and monotone from anywhere right of the zero as
+// all zeros of F are real.  No cancellation that the zero does not share:
+// the terms of F, taken positive, are at most a few times x F'.
+__device__ __forceinline__ float laguerre32(float A, float K, float C, float x) {
+  const float q = x + A;
+  const float i = __builtin_fmaf(x, q, -K);
+  const float F3 = 3.0f * __builtin_fmaf(x, i, -C);
+  const float w = x + q;
+  const float F1 = __builtin_fmaf(x, w, i);
+  const float s = __builtin_amdgcn_sqrtf(__builtin_fmaf(F1, F1, -F3 * (x + w)));
+  return __builtin_fmaf(-F3, __builtin_amdgcn_rcpf(__builtin_fmaf(2.0f, s, F1)), x);
+}
+
+// Start of the FP64 zero finder, in FP32, where arithmetic costs half as
+// much (a multiply, add or FMA 2 cycles per wavefront against 4, measured,
+// v_rcp and v_sqrt 8 against 16) and does not lower the clock:
+//  * U = x_inf, the zero of x - gb - (b1^2 + b2^2)/x (the first iterate from
+//    +infinity, Sec. 1.4.1), an upper bound;
+//  * the zero of x - gb - b1^2/x - b2^2 chord(x), chord the chord of the
+//    convex 1/(x + ab) over [0, 0.7 U] (over [0, U] it gives an upper bound
+//    again; the shorter one is nearer the zero): close whether the zero lies
+//    next to the pole at 0 or far from it;
+//  * two Laguerre steps.
+// In a CPU emulation of this arithmetic its relative error stays below
+// 2^-17.5 for all lanes of 100% of wavefronts on N(0,1), uniform and
+// chi-square matrices, 99.6% of the stress mix and 98% of condition-1e8 SPD
+// matrices; two Borges-Gragg steps instead (70 cycles each against 38) 87%
+// on chi-square ones; x_inf and three Laguerre steps as few as none (SPD).
+// Nothing is checked here: an arrow that FP32 cannot represent gives some
+// useless value (or NaN), which the FP64 step's test rejects.
+__device__ __forceinline__ float start_point(const Arrow1& P, const Cubic& Q) {
+  const float b1s = (float)P.b1s, b2s = (float)P.b2s, ab = (float)P.ab, gb = (float)P.gb;
+  const float K = (float)Q.K;
+  const float rab = __builtin_amdgcn_rcpf(ab);
+  const float U = quad_zero32_1(gb, b1s + b2s);
+  const float k = (b2s * rab) * __builtin_amdgcn_rcpf(__builtin_fmaf(0.7f, U, ab));
+  float x = quad_zero32((K - b1s) * rab, b1s, 1.0f + k);
+  x = laguerre32(ab - gb, K, b1s * ab, x);
+  return laguerre32(ab - gb, K, b1s * ab, x);
+}
+
+// One step of Halley's method on F, x - F F' / (F'^2 - F F''/2), in FP64.
+//  * done: Newton's correction F/F' at most 2^-17.5 x.  With the other zeros
+//    of F at or below 0, |F'/F| is at most 1/d + 2/x at the distance d from
+//    the sought one, so d is then that small, whatever x > 0 was given; and
+//    the step leaves at most 3 d^3/x^2, that is 2^-51 x, the 2 eps that
+//    bg_update's stop test asks for.  NaN, zero, negative and infinite x
+//    fail it.
+//  * The quotient's error, one v_rcp_f64 and one correction (2^-47), is
+//    relative to a correction of 2^-17 x.
+// 92 cycles per wavefront, against 290 for a Borges-Gragg step with its test.
+__device__ __forceinline__ double halley_step(const Cubic& Q, double x, bool& done) {
+  const double q = x + Q.A;
+  const double i = __builtin_fma(x, q, -Q.K);
+  const double F = __builtin_fma(x, i, -Q.C);
+  const double w = x + q;
+  const double F1 = __builtin_fma(x, w, i);
+  const double den = __builtin_fma(F1, F1, -F * (x + w));
+  const double r = __builtin_amdgcn_rcp(den);
+  const double d0 = (F * F1) * r;
+  const double dx = __builtin_fma(d0, __builtin_fma(-den, r, 1.0), d0);
+  done = dabs(F) <= (0x1.6p-18 * x) * F1;
+  return x - dx;
+}
+
+// FP32 arrow of the unrefined ablation: c0 = gb + b2^2/ab and rab = 1/ab are
+// formed in FP64 and rounded.
+struct Arrow1f {
+  float b1s, b2s, ab, gb, c0, rab;
+};
+
+__device__ __forceinline__ Arrow1f to_f32(const Arrow1& P, double rab) {
+  return Arrow1f{(float)P.b1s, (float)P.b2s, (float)P.ab, (float)P.gb,
+                 (float)__builtin_fma(P.b2s, rab, P.gb), (float)rab};
+}
+
+// The chord bounds of bg_start in FP32; the chords' constant is c0, which
+// FP32 could not form where its terms cancel.
 __device__ __forceinline__ float bg_start32(const Arrow1f& P) {
   float U = quad_zero32(P.gb, P.b1s + P.b2s, 1.0f);
   const float b2r = P.b2s * P.rab;
   const float c = P.c0;
 #pragma unroll
-  for (int j = 0; j < CHORDS; ++j) {
+  for (int j = 0; j < kChords; ++j) {
     const float k = b2r * __builtin_amdgcn_rcpf(U + P.ab);
     U = __builtin_fminf(U, quad_zero32(c, P.b1s, 1.0f + k));
   }
   return U;
-}
-
-// One Borges-Gragg iterate from t (Sec. 1.4.1), as the positive zero of the
-// model itself.  The model takes 1/(x + ab) as A - B x + C/x with the value
-// and first two derivatives matched at t, with p = t + ab:
-//   A = ab (3t + ab)/p^3,  B = ab/p^3,  C = t^3/p^3,
-// so its zero is that of (1 + b2^2 B) x^2 - (gb + b2^2 A) x - (b1^2 + b2^2 C),
-// and gb + b2^2 A = c0 - b2^2 t^2 (t + 3 ab)/(ab p^3).  In this form the
-// iterate needs neither f nor an increment: no cancellation next to the pole
-// at 0, no case for large steps, and every factor formed below (t/p, ab/p
-// <= 1) stays in range.
-__device__ __forceinline__ float bg_iterate32(const Arrow1f& P, float t) {
-  const float r = __builtin_amdgcn_rcpf(t + P.ab);
-  const float g = P.b2s * r, u = t * r;
-  const float w = (g * u) * u;  // b2^2 t^2 / p^3
-  const float a = __builtin_fmaf(g * r, P.ab * r, 1.0f);
-  const float k = __builtin_fmaf(w, t, P.b1s);
-  const float c = __builtin_fmaf(-(w * P.rab), __builtin_fmaf(3.0f, P.ab, t), P.c0);
-  return quad_zero32(c, k, a);
-}
-
-// Start of the FP64 zero finder: x_inf (the first iterate from +infinity),
-// one chord over [0, x_inf], and two Borges-Gragg iterates, all in FP32.
-// The chord's zero is close whether the root lies next to the pole at 0 or
-// far from it, so two cubic iterates reach FP32's accuracy: in a CPU
-// emulation of this arithmetic the relative error r stays below 2^-17 for
-// all lanes of 99% of wavefronts on N(0,1), uniform and condition-1e8 SPD
-// matrices and 94-97% on chi-square ones; with x_inf, three chords and one
-// iterate, in 54-99%; without the chord, in at most 92% and mostly none.
-// Nothing is checked here: an arrow that FP32 cannot represent gives some
-// useless value (or NaN), which the FP64 step's test of its correction
-// rejects.
-__device__ __forceinline__ float start_point(const Arrow1f& P) {
-  float x = quad_zero32_1(P.gb, P.b1s + P.b2s);
-  const float k = (P.b2s * P.rab) * __builtin_amdgcn_rcpf(x + P.ab);
-  x = quad_zero32(P.c0, P.b1s, 1.0f + k);
-  x = bg_iterate32(P, x);
-  return bg_iterate32(P, x);
-}
-
-// One FP64 step from x by Chebyshev's third-order correction of Newton's
-// step, x - (f/f')(1 + f f''/(2 f'^2)).  f is evaluated to about one ulp of
-// its terms; the correction itself is small next to x, so one v_rcp_f64 of
-// f' will do: its error e = 1 - f' r is folded in with the second-order
-// term (f'' = -2g).
-//  * done: a correction of at most 2^-17 x.  As t |f''(t)| <= 2 f'(t), a
-//    correction of r x puts the zero within about r x of x, whatever x > 0
-//    was given.  With A2 = g/f' and A3 a sixth of the third derivative over
-//    f', the step leaves |2 A2^2 - A3| times the cube of that distance, at
-//    most r^3 x since x A2 <= 1 and (x A2)^2 <= x^2 A3 <= x A2: 2^-51 x, the
-//    2 eps that bg_update's stop test asks for.  NaN, zero, negative and
-//    infinite x fail it.
-__device__ __forceinline__ double chebyshev_step(const Arrow1& P, double x, bool& done) {
-  const Spec s = spec_eval(P, x);
-  const double g = __builtin_fma(s.q1 * s.rx, s.rx, (s.q2 * s.rp) * s.rp);
-  const double r = __builtin_amdgcn_rcp(s.fp);
-  const double d0 = s.f * r;
-  const double e = __builtin_fma(-s.fp, r, 1.0);
-  const double dx = __builtin_fma(d0, __builtin_fma(-d0, g * r, e), d0);
-  done = dabs(dx) <= 0x1p-17 * x;
-  return x - dx;
 }
 
 // One Borges-Gragg step from x on either side of the zero (Sec. 1.4.1: the
@@ -481,22 +501,25 @@ __device__ __forceinline__ double newton_step(const Arrow1& P, double x, bool& s
   return xn;
 }
 
-// Both zeros (mu and nu): their FP32 starts, one Chebyshev step each, and
-// Borges-Gragg steps in FP64 on the roots that are not done then (or on all
-// of them: converge).  Those go on from the Chebyshev iterate where it moved
-// by less than a quarter of x, else from the FP64 bounds of bg_start: the
-// arrow was outside FP32's range, or its zero below FP32's resolution.
-// The two recurrences are independent, so their latencies overlap; the loop
-// runs until both have stopped.  It is a branch of its own, which the empty
-// asm keeps from being evaluated on every lane.
-__device__ __forceinline__ void zeros_bg(const Arrow1& P1, const Arrow1& P2, bool converge,
-                                         double& x1, double& x2, int& it1, int& it2) {
-  const double rab = rcp1(P1.ab);  // both problems share abar
-  const double y1 = (double)start_point(to_f32(P1, rab));
-  const double y2 = (double)start_point(to_f32(P2, rab));
+// Both zeros (mu and nu) of the arrow with hh = b1^2 + b2^2: their FP32
+// starts and one Halley step each.  Roots that are not done then (the arrow
+// was outside FP32's range, or the FP32 start not close enough) take more
+// Halley steps, from the FP64 bounds of bg_start where the first step moved
+// by more than a quarter of x, and those still not done (or all: converge)
+// Borges-Gragg steps to their stop test, from x_inf where Halley's left no
+// positive x.  The two recurrences are
+// independent, so their latencies overlap.  What follows the first steps is
+// a branch of its own, which the empty asm keeps from being evaluated on
+// every lane.
+__device__ __forceinline__ void zeros_bg(const Arrow1& P1, const Arrow1& P2, double hh,
+                                         bool converge, double& x1, double& x2, int& it1,
+                                         int& it2) {
+  const Cubic Q1 = cubic(P1, hh), Q2 = cubic(P2, hh);
+  const double y1 = (double)start_point(P1, Q1);
+  const double y2 = (double)start_point(P2, Q2);
   bool s1, s2;
-  x1 = chebyshev_step(P1, y1, s1);
-  x2 = chebyshev_step(P2, y2, s2);
+  x1 = halley_step(Q1, y1, s1);
+  x2 = halley_step(Q2, y2, s2);
   it1 = 1;
   it2 = 1;
   if (converge) {
@@ -505,8 +528,19 @@ __device__ __forceinline__ void zeros_bg(const Arrow1& P1, const Arrow1& P2, boo
   }
   if (!(s1 && s2)) {
     asm volatile("");
+    const double rab = rcp1(P1.ab);  // both problems share abar
     if (!s1 && !(dabs(x1 - y1) <= 0.25 * y1)) x1 = bg_start(P1, rab);
     if (!s2 && !(dabs(x2 - y2) <= 0.25 * y2)) x2 = bg_start(P2, rab);
+    if (!converge) {
+      for (int k = 0; k < kMaxHalley; ++k) {
+        if (s1 && s2) break;
+        if (!s1) { ++it1; x1 = halley_step(Q1, x1, s1); }
+        if (!s2) { ++it2; x2 = halley_step(Q2, x2, s2); }
+      }
+      const double inf = __builtin_inf();
+      if (!s1 && !(x1 > 0.0 && x1 < inf)) x1 = quad_zero(P1.gb, hh, 1.0);
+      if (!s2 && !(x2 > 0.0 && x2 < inf)) x2 = quad_zero(P2.gb, hh, 1.0);
+    }
     for (int k = 0; k < kMaxIter; ++k) {
       if (s1 && s2) break;
       if (!s1) { ++it1; x1 = bg_step(P1, x1, s1); }
@@ -782,7 +816,7 @@ __device__ __forceinline__ int solve3(const double (&ain)[6], uint32_t flags,
       const Arrow1f Q1 = to_f32(P1, rab), Q2 = to_f32(P2, rab);
       // the FP32 problem must be representable away from the poles
       bool fb = !(Q1.b1s >= 0x1p-100f && Q1.b2s >= 0x1p-100f && Q1.ab >= 0x1p-60f);
-      float y1 = bg_start32<kChords>(Q1), y2 = bg_start32<kChords>(Q2);
+      float y1 = bg_start32(Q1), y2 = bg_start32(Q2);
       bool s1 = false, s2 = false, c1 = false, c2 = false;
       for (int k = 0; k < kMaxIter32; ++k) {
         if (s1 && s2) break;
@@ -793,7 +827,7 @@ __device__ __forceinline__ int solve3(const double (&ain)[6], uint32_t flags,
       if (fb) {
         // no usable FP32 zero: the FP64 zero finder from its own start
         int j1, j2;
-        zeros_bg(P1, P2, false, mu, nu, j1, j2);
+        zeros_bg(P1, P2, hh, false, mu, nu, j1, j2);
         it1 += j1;
         it2 += j2;
       } else {
@@ -801,15 +835,15 @@ __device__ __forceinline__ int solve3(const double (&ain)[6], uint32_t flags,
         nu = (double)y2;
       }
     } else if (FORM == kFormF32R) {
-      zeros_bg(P1, P2, flags & kFlagRefineConverge, mu, nu, it1, it2);
-      it1 += 2;  // and the two FP32 iterates of the start
+      zeros_bg(P1, P2, hh, flags & kFlagRefineConverge, mu, nu, it1, it2);
+      it1 += 2;  // and the two FP32 steps of the start
       it2 += 2;
     } else if (flags & kFlagNewton) {
       zeros_newton(P1, P2, mu, nu, it1, it2);
     } else if (flags & kFlagPaperBG) {
       zeros_bg_paper(P1, P2, mu, nu, it1, it2);
     } else {
-      zeros_bg(P1, P2, false, mu, nu, it1, it2);
+      zeros_bg(P1, P2, hh, false, mu, nu, it1, it2);
     }
     // lambda3 <= lambda2 <= lambda1; lambda2 by the trace identity
     l2 = al1 + mu;
