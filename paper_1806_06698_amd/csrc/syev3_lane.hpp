@@ -188,21 +188,6 @@ __device__ __forceinline__ Spec spec_eval(const Arrow1& P, double x) {
   return s;
 }
 
-// Starting point: an upper bound of the zero, tightened twice.  Each
-// bound is the positive zero of a function that lies below f on an interval
-// holding the zero (f is increasing, so that zero is right of f's).
-//  * U0 = x_inf, the zero of x - gb - (b1^2 + b2^2)/x: the first iterate
-//    from +infinity (Sec. 1.4.1); below f because 1/(x + ab) < 1/x.
-//  * U_{k+1}: the zero of x - gb - b1^2/x - b2^2 chord_k(x), where chord_k
-//    is the chord of the convex 1/(x + ab) over [0, U_k], which lies above
-//    it there, so the function lies below f on (0, U_k].  U_{k+1} is in
-//    [zero, U_k].  Over a wide interval the chord is about 1/ab, which makes
-//    U_1 tight next to the pole at 0, where x_inf can be off by orders of
-//    magnitude; narrower intervals tighten it everywhere.
-// In a CPU emulation of this arithmetic, two chords leave under 1% of zeros
-// needing a third evaluation of f (x_inf alone: 10%); on the GPU two chords
-// time best (one chord costs about what it saves in zero-finder trips from
-// the third on).  rab = 1/ab.
 // quad_zero(c, k, a): positive zero of a x^2 - c x - k (a, k > 0), in the
 // form without cancellation.
 __device__ __forceinline__ double quad_zero(double c, double k, double a) {
@@ -210,21 +195,6 @@ __device__ __forceinline__ double quad_zero(double c, double k, double a) {
   const double s = dabs(c2) + sqrt1(__builtin_fma(c2, c2, a * k));
   const bool pos = c >= 0.0;
   return (pos ? s : k) * rcp1(pos ? a : s);
-}
-
-constexpr int kChords = 2;
-
-__device__ __forceinline__ double bg_start(const Arrow1& P, double rab) {
-  double U = quad_zero(P.gb, P.b1s + P.b2s, 1.0);
-  const double b2r = P.b2s * rab;
-  const double c = P.gb + b2r;
-#pragma unroll
-  for (int j = 0; j < kChords; ++j) {
-    // chord of 1/(x + ab) over [0, U]: 1/ab - x / (ab (U + ab))
-    const double k = b2r * rcp1(U + P.ab);
-    U = __builtin_fmin(U, quad_zero(c, P.b1s, 1.0 + k));
-  }
-  return U;
 }
 
 // FP32 versions (v_rcp_f32 and v_sqrt_f32 are accurate to about one ulp),
@@ -310,8 +280,8 @@ __device__ __forceinline__ float start_point(const Arrow1& P, const Cubic& Q) {
 //    of F at or below 0, |F'/F| is at most 1/d + 2/x at the distance d from
 //    the sought one, so d is then that small, whatever x > 0 was given; and
 //    the step leaves at most 3 d^3/x^2, that is 2^-51 x, the 2 eps that
-//    bg_update's stop test asks for.  NaN, zero, negative and infinite x
-//    fail it.
+//    bg_update's stop test asks for.  NaN, zero, infinite and (as F' has to
+//    be positive) negative x fail it.
 //  * The quotient's error, one v_rcp_f64 and one correction (2^-47), is
 //    relative to a correction of 2^-17 x.
 // 92 cycles per wavefront, against 290 for a Borges-Gragg step with its test.
@@ -325,8 +295,29 @@ __device__ __forceinline__ double halley_step(const Cubic& Q, double x, bool& do
   const double r = __builtin_amdgcn_rcp(den);
   const double d0 = (F * F1) * r;
   const double dx = __builtin_fma(d0, __builtin_fma(-den, r, 1.0), d0);
-  done = dabs(F) <= (0x1.6p-18 * x) * F1;
+  done = dabs(F) <= (0x1.6p-18 * x) * F1 && F1 > 0.0;
   return x - dx;
+}
+
+// The start in FP64, for arrows that FP32 cannot represent: its range, not
+// its precision, is what a zero needs that is many orders of magnitude below
+// the matrix (a nearly isotropic matrix, or tiny betas).
+__device__ __forceinline__ double laguerre(const Cubic& Q, double x) {
+  const double q = x + Q.A;
+  const double i = __builtin_fma(x, q, -Q.K);
+  const double F3 = 3.0 * __builtin_fma(x, i, -Q.C);
+  const double w = x + q;
+  const double F1 = __builtin_fma(x, w, i);
+  const double D = __builtin_fmax(0x1p-1000, __builtin_fma(F1, F1, -F3 * (x + w)));
+  return __builtin_fma(-F3, rcp1(__builtin_fma(2.0, sqrt1(D), F1)), x);
+}
+
+__device__ __forceinline__ double start_point64(const Arrow1& P, const Cubic& Q) {
+  const double rab = rcp1(P.ab);
+  const double U = quad_zero(P.gb, P.b1s + P.b2s, 1.0);
+  const double k = (P.b2s * rab) * rcp1(__builtin_fma(0.7, U, P.ab));
+  const double x = quad_zero((Q.K - P.b1s) * rab, P.b1s, 1.0 + k);
+  return laguerre(Q, laguerre(Q, x));
 }
 
 // FP32 arrow of the unrefined ablation: c0 = gb + b2^2/ab and rab = 1/ab are
@@ -340,8 +331,10 @@ __device__ __forceinline__ Arrow1f to_f32(const Arrow1& P, double rab) {
                  (float)__builtin_fma(P.b2s, rab, P.gb), (float)rab};
 }
 
-// The chord bounds of bg_start in FP32; the chords' constant is c0, which
-// FP32 could not form where its terms cancel.
+// An upper bound of the zero: x_inf, tightened by chords of 1/(x + ab) over
+// [0, U] (see start_point); their constant is c0, which FP32 could not form
+// where its terms cancel.
+constexpr int kChords = 2;
 __device__ __forceinline__ float bg_start32(const Arrow1f& P) {
   float U = quad_zero32(P.gb, P.b1s + P.b2s, 1.0f);
   const float b2r = P.b2s * P.rab;
@@ -501,22 +494,34 @@ __device__ __forceinline__ double newton_step(const Arrow1& P, double x, bool& s
   return xn;
 }
 
-// Both zeros (mu and nu) of the arrow with hh = b1^2 + b2^2: their FP32
-// starts and one Halley step each.  Roots that are not done then (the arrow
-// was outside FP32's range, or the FP32 start not close enough) take more
-// Halley steps, from the FP64 bounds of bg_start where the first step moved
-// by more than a quarter of x, and those still not done (or all: converge)
-// Borges-Gragg steps to their stop test, from x_inf where Halley's left no
-// positive x.  The two recurrences are
-// independent, so their latencies overlap.  What follows the first steps is
-// a branch of its own, which the empty asm keeps from being evaluated on
-// every lane.
-__device__ __forceinline__ void zeros_bg(const Arrow1& P1, const Arrow1& P2, double hh,
-                                         bool converge, double& x1, double& x2, int& it1,
-                                         int& it2) {
-  const Cubic Q1 = cubic(P1, hh), Q2 = cubic(P2, hh);
-  const double y1 = (double)start_point(P1, Q1);
-  const double y2 = (double)start_point(P2, Q2);
+// The two problems of an ordered, reduced arrow (Sec. 1.2): mu is the
+// rightmost zero of A - alpha1 I, nu that of P (alpha2 I - A) P.
+// g1 = gamma - alpha1, g2 = alpha2 - gamma.
+struct Arrows {
+  Arrow1 mu, nu;
+};
+
+__device__ __forceinline__ Arrows arrows(double al, double be1, double be2, double g1,
+                                         double g2) {
+  const double b1s = be1 * be1, b2s = be2 * be2;
+  return Arrows{Arrow1{b1s, b2s, al, g1}, Arrow1{b2s, b1s, al, g2}};
+}
+
+// Both zeros: their FP32 starts and one Halley step each.  Roots that are
+// not done then take more Halley steps, from the start in FP64 where the
+// first one moved by more than a quarter of x, and those still not done (or
+// all: converge) Borges-Gragg steps to their stop test, from x_inf where
+// Halley's left no positive x.  The two recurrences are independent, so
+// their latencies overlap.  What follows the first steps is a branch of its
+// own, which the empty asm keeps from being evaluated on every lane; it
+// forms the arrows again, so that they need not be held until there.
+__device__ __forceinline__ void zeros_bg(double al, double be1, double be2, double g1,
+                                         double g2, double hh, bool converge, double& x1,
+                                         double& x2, int& it1, int& it2) {
+  const Arrows P = arrows(al, be1, be2, g1, g2);
+  const Cubic Q1 = cubic(P.mu, hh), Q2 = cubic(P.nu, hh);
+  const double y1 = (double)start_point(P.mu, Q1);
+  const double y2 = (double)start_point(P.nu, Q2);
   bool s1, s2;
   x1 = halley_step(Q1, y1, s1);
   x2 = halley_step(Q2, y2, s2);
@@ -527,24 +532,31 @@ __device__ __forceinline__ void zeros_bg(const Arrow1& P1, const Arrow1& P2, dou
     s1 = s2 = false;
   }
   if (!(s1 && s2)) {
-    asm volatile("");
-    const double rab = rcp1(P1.ab);  // both problems share abar
-    if (!s1 && !(dabs(x1 - y1) <= 0.25 * y1)) x1 = bg_start(P1, rab);
-    if (!s2 && !(dabs(x2 - y2) <= 0.25 * y2)) x2 = bg_start(P2, rab);
+    asm volatile("" : "+v"(be1), "+v"(be2));
+    const Arrows R = arrows(al, be1, be2, g1, g2);
+    const Cubic C1 = cubic(R.mu, hh), C2 = cubic(R.nu, hh);
+    if (!s1 && !(dabs(x1 - y1) <= 0.25 * y1)) {
+      asm volatile("");
+      x1 = start_point64(R.mu, C1);
+    }
+    if (!s2 && !(dabs(x2 - y2) <= 0.25 * y2)) {
+      asm volatile("");
+      x2 = start_point64(R.nu, C2);
+    }
     if (!converge) {
-      for (int k = 0; k < kMaxHalley; ++k) {
+      for (int t = 0; t < kMaxHalley; ++t) {
         if (s1 && s2) break;
-        if (!s1) { ++it1; x1 = halley_step(Q1, x1, s1); }
-        if (!s2) { ++it2; x2 = halley_step(Q2, x2, s2); }
+        if (!s1) { ++it1; x1 = halley_step(C1, x1, s1); }
+        if (!s2) { ++it2; x2 = halley_step(C2, x2, s2); }
       }
       const double inf = __builtin_inf();
-      if (!s1 && !(x1 > 0.0 && x1 < inf)) x1 = quad_zero(P1.gb, hh, 1.0);
-      if (!s2 && !(x2 > 0.0 && x2 < inf)) x2 = quad_zero(P2.gb, hh, 1.0);
+      if (!s1 && !(x1 > 0.0 && x1 < inf)) x1 = quad_zero(R.mu.gb, hh, 1.0);
+      if (!s2 && !(x2 > 0.0 && x2 < inf)) x2 = quad_zero(R.nu.gb, hh, 1.0);
     }
-    for (int k = 0; k < kMaxIter; ++k) {
+    for (int t = 0; t < kMaxIter; ++t) {
       if (s1 && s2) break;
-      if (!s1) { ++it1; x1 = bg_step(P1, x1, s1); }
-      if (!s2) { ++it2; x2 = bg_step(P2, x2, s2); }
+      if (!s1) { ++it1; x1 = bg_step(R.mu, x1, s1); }
+      if (!s2) { ++it2; x2 = bg_step(R.nu, x2, s2); }
     }
   }
 }
@@ -662,25 +674,11 @@ __device__ __forceinline__ Vec3 normalized(Vec3 u) {
   return Vec3{u.x * r, u.y * r, u.z * r};
 }
 
-__device__ __forceinline__ Vec3 axpy(double s, const Vec3& a, const Vec3& b) {
-  return Vec3{__builtin_fma(s, a.x, b.x), __builtin_fma(s, a.y, b.y),
-              __builtin_fma(s, a.z, b.z)};
-}
-
-// max(|x|, |y|) and max(x, y) as one v_max_f64 each.  Written with
-// __builtin_fmax, each input loaded from memory first gets a canonicalising
-// v_max_f64 x, x of its own (fmax must quiet a signalling NaN), 11
-// instructions for the six-entry maximum instead of 5.  The maximum only
-// sets the scaling exponent; a NaN input is caught by the finiteness test.
-__device__ __forceinline__ double vmax_abs(double x, double y) {
-  double r;
-  asm("v_max_f64 %0, |%1|, |%2|" : "=v"(r) : "v"(x), "v"(y));
-  return r;
-}
-__device__ __forceinline__ double vmax(double x, double y) {
-  double r;
-  asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(x), "v"(y));
-  return r;
+// The high word of |x|: sign cleared, exponent in its upper 11 bits.  Among
+// finite numbers it orders by exponent, and it is at least 0x7ff00000 for
+// infinities and NaNs alone.
+__device__ __forceinline__ uint32_t abs_hi(double x) {
+  return (uint32_t)(__builtin_bit_cast(uint64_t, x) >> 32) & 0x7fffffffu;
 }
 
 template <bool VECS, int FORM>
@@ -688,21 +686,32 @@ __device__ __forceinline__ int solve3(const double (&ain)[6], uint32_t flags,
                                       double (&lam)[3], double (&V)[9], bool& bad) {
   double a11 = ain[0], a12 = ain[1], a13 = ain[2], a22 = ain[3], a23 = ain[4],
          a33 = ain[5];
-  const bool finite = __builtin_isfinite(a11) && __builtin_isfinite(a12) &&
-                      __builtin_isfinite(a13) && __builtin_isfinite(a22) &&
-                      __builtin_isfinite(a23) && __builtin_isfinite(a33);
+  // Scale by 2^-e so that max |a_ij| is in [1/2, 1); a zero matrix keeps
+  // e = 0.  The exponent and the test for NaN and infinity come from the
+  // largest high word: six ANDs at 2 cycles per wavefront and three integer
+  // maxima, where six v_cmp and five v_max_f64 took 4 each (the maxima of
+  // loaded doubles would be canonicalised besides).
+  const uint32_t hi = max(max(max(abs_hi(a11), abs_hi(a12)), max(abs_hi(a13), abs_hi(a22))),
+                          max(abs_hi(a23), abs_hi(a33)));
   // Kept as a word from here on: left as a condition the compiler re-derives
-  // it at the stores from the six inputs, holding them through the solve.
-  uint32_t badw = finite ? 0u : 1u;
+  // it at the stores, holding its input through the solve.
+  uint32_t badw = hi >= 0x7ff00000u ? 1u : 0u;
   asm volatile("" : "+v"(badw));
   bad = badw != 0u;
-  const double m = vmax(vmax(vmax_abs(a11, a12), vmax_abs(a13, a22)), vmax_abs(a23, a33));
-  // scale by 2^-e so that max |a_ij| is in [1/2, 1); m == 0 keeps e = 0
-  // (kFlagNoScale, a uniform flag: e = 0, the unscaled matrix)
+  int e = (int)(hi >> 20) - 1022;
+  bool zero = false;
+  if (hi < 0x00100000u) {
+    // zero, or every entry subnormal: a branch of its own (the empty asm)
+    asm volatile("");
+    const double m = __builtin_fmax(
+        __builtin_fmax(__builtin_fmax(dabs(a11), dabs(a12)), __builtin_fmax(dabs(a13), dabs(a22))),
+        __builtin_fmax(dabs(a23), dabs(a33)));
+    e = __builtin_amdgcn_frexp_exp(m);
+    zero = m == 0.0;
+  }
   // (The flags are the same for every lane: their alternatives are taken in
   // uniform branches, which the empty asm keeps the compiler from turning
   // into per-lane selects that every lane would pay for.)
-  int e = __builtin_amdgcn_frexp_exp(m);
   if (flags & kFlagNoScale) {
     asm volatile("");
     e = 0;
@@ -717,22 +726,11 @@ __device__ __forceinline__ int solve3(const double (&ain)[6], uint32_t flags,
   // Sec. 1: ordered arrow
   const Rot2 J = rot2(a11, a12, a22);
   const double al1 = J.l1, al2 = J.l2;
-  const double be1 = __builtin_fma(J.k11, a13, J.k21 * a23);
-  const double be2 = __builtin_fma(J.k12, a13, J.k22 * a23);
+  double be1 = __builtin_fma(J.k11, a13, J.k21 * a23);
+  double be2 = __builtin_fma(J.k12, a13, J.k22 * a23);
   const double ga = a33;
 
   // Sec. 1.1: h = ||beta||, the Givens rotation G and the deflation test.
-  // h <= eps (|alpha1| + |alpha2| + |gamma|) is tested as h^2 <= (eps ...)^2.
-  const double hh = __builtin_fma(be1, be1, be2 * be2);
-  const double tol_h = kEps64 * (dabs(al1) + dabs(al2) + dabs(ga));
-  bool diag;
-  if (flags & kFlagNoHGuard) {
-    asm volatile("");
-    diag = hh == 0.0;
-  } else {
-    diag = !(hh > tol_h * tol_h);
-  }
-  const double al = al1 - al2;
   // The test |e| <= eps (|d1| + |d2|) on G A G^T, whose off-diagonal entry
   // is e = alpha sg cg and whose diagonal is d1 = alpha1 cg^2 + alpha2 sg^2,
   // d2 = alpha1 sg^2 + alpha2 cg^2 (sg = beta1/h, cg = beta2/h), taken
@@ -741,15 +739,57 @@ __device__ __forceinline__ int solve3(const double (&ain)[6], uint32_t flags,
   // G itself is formed only on lanes that deflate.  The exact beta- and
   // combo-deflations (beta1, beta2 or alpha zero) make the left side zero.
   const double b1s = be1 * be1, b2s = be2 * be2;
+  double hh = __builtin_fma(be1, be1, b2s);
+  double al = al1 - al2, g1 = ga - al1, g2 = al2 - ga;
   const double ee = al * be1 * be2;
-  double rhs;
-  if (flags & kFlagSimplified) {
+  bool diag = false, defl = false;
+  double unscale = 1.0;
+  // In the scaled matrix |alpha1|, |alpha2| <= 2 and h^2 < 2, so the right
+  // side is below 8 eps = 2^-49 and h^2 >= |ee|/2: a left side above 2^-48
+  // neither deflates nor has a negligible h, and a wavefront all of whose
+  // lanes are there (all N(0,1), uniform and condition-1e8 SPD ones) skips
+  // the tests, 44 cycles.  (An unscaled matrix has no such bounds.)
+  if (!(dabs(ee) > 0x1p-48) || (flags & kFlagNoScale)) {
     asm volatile("");
-    rhs = dabs(al1 + al2) * hh;
-  } else {
-    rhs = dabs(__builtin_fma(al1, b2s, al2 * b1s)) + dabs(__builtin_fma(al1, b1s, al2 * b2s));
+    // h <= eps (|alpha1| + |alpha2| + |gamma|) is tested as h^2 <= (eps ...)^2
+    const double tol_h = kEps64 * (dabs(al1) + dabs(al2) + dabs(ga));
+    if (flags & kFlagNoHGuard) {
+      asm volatile("");
+      diag = hh == 0.0;
+    } else {
+      diag = !(hh > tol_h * tol_h);
+    }
+    double rhs;
+    if (flags & kFlagSimplified) {
+      asm volatile("");
+      rhs = dabs(al1 + al2) * hh;
+    } else {
+      rhs =
+          dabs(__builtin_fma(al1, b2s, al2 * b1s)) + dabs(__builtin_fma(al1, b1s, al2 * b2s));
+    }
+    defl = !diag && dabs(ee) <= kEps64 * rhs;
+    // An arrow far smaller than the matrix it came from (a nearly isotropic
+    // one) is scaled up by a power of two, alpha1, alpha2 and gamma through
+    // their differences, so that the zero finder's FP32 start can hold the
+    // fourth power of its size: isotropic + 1e-12 N(0,1) then takes one
+    // Halley step like any other matrix (2^22 eigenvalues 52 us, against 91
+    // from the start in FP64).  The vectors do not change by it, and the
+    // zeros are scaled back where they are added to alpha1, alpha2 and
+    // gamma.  (Where the tests are skipped the arrow's size is at least the
+    // cube root of 2^-48.)
+    const double size2 = __builtin_fma(g1, g1, __builtin_fma(g2, g2, hh));
+    if (!diag && !defl && !(size2 >= 0x1p-30 && size2 <= 0x1p30)) {
+      asm volatile("");
+      const int k = __builtin_amdgcn_frexp_exp(size2) >> 1;
+      al = __builtin_amdgcn_ldexp(al, -k);
+      be1 = __builtin_amdgcn_ldexp(be1, -k);
+      be2 = __builtin_amdgcn_ldexp(be2, -k);
+      g1 = __builtin_amdgcn_ldexp(g1, -k);
+      g2 = __builtin_amdgcn_ldexp(g2, -k);
+      hh = __builtin_amdgcn_ldexp(hh, -2 * k);
+      unscale = __builtin_amdgcn_ldexp(1.0, k);
+    }
   }
-  const bool defl = !diag && dabs(ee) <= kEps64 * rhs;
 
   double l0, l1, l2;  // ascending
   Vec3 v0, v1, v2;    // their eigenvectors, arrow coordinates
@@ -805,11 +845,10 @@ __device__ __forceinline__ int solve3(const double (&ain)[6], uint32_t flags,
     }
   } else {
     branch = kReduced;
-    // mu: rightmost zero of A - alpha1 I; nu: of P(alpha2 I - A)P
-    const Arrow1 P1{b1s, b2s, al, ga - al1};
-    const Arrow1 P2{b2s, b1s, al, al2 - ga};
     double mu = 0.0, nu = 0.0;
     if (FORM == kFormF32) {
+      const Arrows P = arrows(al, be1, be2, g1, g2);
+      const Arrow1 &P1 = P.mu, &P2 = P.nu;
       // The unrefined FP32 ablation: Borges-Gragg in FP32 from the FP32
       // two-chord start, its zeros used as they are.
       const double rab = rcp1(P1.ab);  // both problems share abar
@@ -827,7 +866,7 @@ __device__ __forceinline__ int solve3(const double (&ain)[6], uint32_t flags,
       if (fb) {
         // no usable FP32 zero: the FP64 zero finder from its own start
         int j1, j2;
-        zeros_bg(P1, P2, hh, false, mu, nu, j1, j2);
+        zeros_bg(al, be1, be2, g1, g2, hh, false, mu, nu, j1, j2);
         it1 += j1;
         it2 += j2;
       } else {
@@ -835,33 +874,29 @@ __device__ __forceinline__ int solve3(const double (&ain)[6], uint32_t flags,
         nu = (double)y2;
       }
     } else if (FORM == kFormF32R) {
-      zeros_bg(P1, P2, hh, flags & kFlagRefineConverge, mu, nu, it1, it2);
+      zeros_bg(al, be1, be2, g1, g2, hh, flags & kFlagRefineConverge, mu, nu, it1, it2);
       it1 += 2;  // and the two FP32 steps of the start
       it2 += 2;
     } else if (flags & kFlagNewton) {
-      zeros_newton(P1, P2, mu, nu, it1, it2);
+      const Arrows P = arrows(al, be1, be2, g1, g2);
+      zeros_newton(P.mu, P.nu, mu, nu, it1, it2);
     } else if (flags & kFlagPaperBG) {
-      zeros_bg_paper(P1, P2, mu, nu, it1, it2);
+      const Arrows P = arrows(al, be1, be2, g1, g2);
+      zeros_bg_paper(P.mu, P.nu, mu, nu, it1, it2);
     } else {
-      zeros_bg(P1, P2, hh, false, mu, nu, it1, it2);
+      zeros_bg(al, be1, be2, g1, g2, hh, false, mu, nu, it1, it2);
     }
     // lambda3 <= lambda2 <= lambda1; lambda2 by the trace identity
-    l2 = al1 + mu;
-    l0 = al2 - nu;
-    l1 = __builtin_fmin(__builtin_fmax((ga - mu) + nu, l0), l2);
+    l2 = __builtin_fma(mu, unscale, al1);
+    l0 = __builtin_fma(-nu, unscale, al2);
+    l1 = __builtin_fma(nu, unscale, __builtin_fma(-mu, unscale, ga));
+    l1 = __builtin_fmin(__builtin_fmax(l1, l0), l2);
     if (VECS) {
       const double mua = mu + al, nua = nu + al;
       const Vec3 u1{be1 * mua, be2 * mu, mu * mua};
       const Vec3 u3{be1 * nu, be2 * nua, -nu * nua};
-      if (FORM == kFormF32R) {
-        // one Gram-Schmidt re-orthogonalisation of u3 against the unit u1,
-        // before u3 is normalised
-        v2 = normalized(u1);
-        v0 = normalized(axpy(-dot(v2, u3), v2, u3));
-      } else {
-        v2 = normalized(u1);
-        v0 = normalized(u3);
-      }
+      v2 = normalized(u1);
+      v0 = normalized(u3);
       if (FORM == kFormF32) {
         // the ablation keeps the paper's formula for u2
         const Vec3 u2{-be2 * mu * nua, be1 * nu * mua, be1 * be2 * al};
@@ -893,9 +928,9 @@ __device__ __forceinline__ int solve3(const double (&ain)[6], uint32_t flags,
     V[7] = v1.z;
     V[8] = v2.z;
   }
-  if (!finite) {
+  if (bad) {
     branch = kNonFinite;
-  } else if (m == 0.0) {
+  } else if (zero) {
     branch = kZero;
   }
   return branch | (it1 << 8) | (it2 << 16);
