@@ -148,7 +148,7 @@ int solve_segments(int32_t nseg, const syev3_segment* segs, hipStream_t stream) 
     if (o != g_seg_out && overlap(o[-1], ra)) return SYEV3_E_ALIAS;
   }
   t.nseg = k;
-  t.reserved = 0;
+  t.cap = SYEV3_SEGMENTS_MAX;
   t.total_tiles = tiles;
   if (tiles == 0) return SYEV3_OK;
   (void)hipGetLastError();  // a stale error is not this call's

@@ -42,18 +42,25 @@ struct Segment {
 hipError_t launch_stream_probe(int64_t n, const void* A, void* lambda, void* V, int dtype,
                                uint32_t mode, hipStream_t stream);
 
-// A tick's table in device memory: header, then the segments in ascending
-// tile_begin order.  Sized for kMaxSegmentsPerTick; only nseg are read.
+// A tick's table: header, then the segments in ascending tile_begin order.
+// In device memory it has room for `cap` segments and each one's tile_begin
+// again, side by side after them (the search for a tile's segment reads 2 KB
+// of consecutive memory for 256 segments, not one line per segment).
 constexpr int kMaxSegmentsPerTick = SYEV3_SERVER_MAX_SEGMENTS;
 struct TickTable {
   int32_t nseg;
-  int32_t reserved;
+  int32_t cap;
   int64_t total_tiles;
   Segment seg[kMaxSegmentsPerTick];
 };
-// Bytes of a table with room for `max_segments` segments.
-inline size_t tick_table_bytes(int max_segments) {
-  return offsetof(TickTable, seg) + sizeof(Segment) * (size_t)max_segments;
+// Bytes of a device table with room for `cap` segments.
+inline size_t tick_table_bytes(int cap) {
+  return offsetof(TickTable, seg) + (sizeof(Segment) + sizeof(int64_t)) * (size_t)cap;
+}
+// The tile_begins of a device table (or its host image).
+template <typename Table>
+__host__ __device__ inline auto* table_begins(Table* t) {
+  return (decltype(&t->total_tiles))(t->seg + t->cap);
 }
 
 // Launch the segment kernel on a table in device memory: grid_blocks
@@ -61,10 +68,24 @@ inline size_t tick_table_bytes(int max_segments) {
 hipError_t launch_segments(const TickTable* table, int32_t grid_blocks,
                            hipStream_t stream);
 
-// The same on the library's fixed per-device table (no allocation): copies
-// host_table (nseg segments, total_tiles > 0) into the table of the stream's
-// device, then launches on it.  The copy is from pageable host memory, which
-// HIP completes before returning.
+// A table small enough to travel as the launch's kernel argument (3600
+// bytes), with nothing to copy first.
+constexpr int kInlineSegments = 56;
+struct InlineTable {
+  int32_t nseg;
+  int32_t cap;
+  int64_t total_tiles;
+  int64_t begin[kInlineSegments];
+  Segment seg[kInlineSegments];
+};
+hipError_t launch_segments_inline(const InlineTable& table, int32_t grid_blocks,
+                                  hipStream_t stream);
+
+// The same for host_table (nseg segments, total_tiles > 0; its cap and what
+// follows the segments are not read) with no allocation: as the kernel's
+// argument up to kInlineSegments segments, else copied into the library's
+// fixed table of the stream's device.  That copy is from pageable host
+// memory, which HIP completes before returning.
 hipError_t launch_segments_noalloc(const TickTable* host_table, hipStream_t stream);
 
 }  // namespace syev3

@@ -470,110 +470,154 @@ hipError_t launch_batched(int64_t n, const void* A, Strides ld, int layout,
 // the request's size: every load and store of the solve is a global access
 // of a scalar base and that offset, as in the batched SoA kernel (empty asm
 // statements keep the bases scalar and the offset 32-bit; only the NaN path
-// forms full addresses).  Every tile solves for vectors, and a request
-// without them (V null, a uniform branch) skips only their stores: with one
-// solve per form the kernel holds two inlined solves, not four, and fits in
-// 62 VGPRs (8 waves per SIMD; four solves needed 84, 5 waves).
-template <int FORM>
-__device__ __forceinline__ void solve_segment_tile(const Segment& s, int64_t t0) {
-  using T = Storage<FORM>;
-  // the table's pointers are generic: cast to global memory, else every
-  // access is a flat one with a 64-bit address per lane
-  using GT = __attribute__((address_space(1))) T;
-  using GC = __attribute__((address_space(1))) char;
-  const int64_t pa = s.lda * (int64_t)sizeof(T), po = s.n * (int64_t)sizeof(T);
-  const GC* A = (const GC*)s.A + t0 * (int64_t)sizeof(T);
-  GC* L = (GC*)s.lambda + t0 * (int64_t)sizeof(T);
-  GC* W = (GC*)s.V + t0 * (int64_t)sizeof(T);
-  const bool vecs = s.V != nullptr;
-  uint32_t off = threadIdx.x * (uint32_t)sizeof(T);
-  asm volatile("" : "+v"(off));
-  double a[6];
+// forms full addresses).  Both forms share one solve, which always forms the
+// vectors: a request's type and whether it wants them (V null) are uniform
+// branches around the loads and stores.  Plain accesses, as most requests'
+// planes share lines (see motion()).  Bound by HBM and the search's latency
+// ahead of each tile's loads: 200 requests of 2^U(0,20) matrices (2^24 in
+// all, half of them in FP32 storage) 366 us, 4.8 TB/s; 481 us with a solve
+// per form, non-temporal accesses, launch order and a search through the
+// segments themselves.
+template <typename T>
+using GlobalT = __attribute__((address_space(1))) T;
+
+// The table's pointers are generic: cast to global memory, else every access
+// is a flat one with a 64-bit address per lane.
+template <typename T, int N>
+__device__ __forceinline__ void load_planes(double (&a)[N], const GlobalT<char>* base,
+                                            int64_t pitch, uint32_t off) {
 #pragma unroll
-  for (int k = 0; k < 6; ++k) {
+  for (int k = 0; k < N; ++k) {
     // each plane's base pinned in scalar registers (else the compiler chains
     // the planes' addresses per lane in 64 bits)
-    const GC* p = A + k * pa;
+    const GlobalT<char>* p = base + k * pitch;
     asm volatile("" : "+s"(p));
-    a[k] = (double)__builtin_nontemporal_load((const GT*)(p + off));
-  }
-  double l[3], v[9];
-  bool bad;
-  solve3<true, FORM>(a, s.flags, l, v, bad);
-  uint32_t soff = off;
-  asm volatile("" : "+v"(soff));
-  GC* lp[3];
-  GC* vp[9];
-#pragma unroll
-  for (int j = 0; j < 3; ++j) {
-    lp[j] = L + j * po;
-    asm volatile("" : "+s"(lp[j]));
-  }
-#pragma unroll
-  for (int k = 0; k < 9; ++k) {
-    vp[k] = W + k * po;
-    asm volatile("" : "+s"(vp[k]));
-  }
-#pragma unroll
-  for (int j = 0; j < 3; ++j) __builtin_nontemporal_store((T)l[j], (GT*)(lp[j] + soff));
-  if (vecs) {
-    uint32_t voff = soff;
-    asm volatile("" : "+v"(voff));
-#pragma unroll
-    for (int k = 0; k < 9; ++k) __builtin_nontemporal_store((T)v[k], (GT*)(vp[k] + voff));
-  }
-  if (bad) {  // a NaN or infinite entry: NaN in every output of the matrix
-#pragma unroll
-    for (int j = 0; j < 3; ++j) __builtin_nontemporal_store(qnan<T>(), (GT*)(lp[j] + soff));
-    if (vecs) {
-#pragma unroll
-      for (int k = 0; k < 9; ++k) __builtin_nontemporal_store(qnan<T>(), (GT*)(vp[k] + soff));
-    }
+    a[k] = (double)*(const GlobalT<T>*)(p + off);
   }
 }
 
-__global__ __launch_bounds__(kBlock) void k_syev3_segments(const TickTable* __restrict__ t) {
-  const int nseg = t->nseg;
-  const int64_t total_tiles = t->total_tiles;
-  // A tile's segment is the last whose tile_begin <= tile (uniform across
-  // the workgroup).  The table is in ascending tile_begin order, so its index
-  // is the count of segments starting at or before the tile, minus one: each
-  // lane tests four segments and ballots count them, kRound per round, with
-  // the four loads in flight together.  A round not all of whose segments
-  // start at or before the tile is the last.  A workgroup's tiles ascend, so
-  // its next search starts at the round that held this tile's segment.
-  constexpr int kRound = 4 * kWave;
+template <typename T, int N>
+__device__ __forceinline__ void store_planes(const double (&x)[N], GlobalT<char>* base,
+                                             int64_t pitch, uint32_t off) {
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    GlobalT<char>* p = base + k * pitch;
+    asm volatile("" : "+s"(p));
+    *(GlobalT<T>*)(p + off) = (T)x[k];
+  }
+}
+
+__device__ __forceinline__ void solve_segment_tile(const Segment& s, int64_t t0) {
+  const bool f32 = s.dtype != kFormF64;
+  const int sh = f32 ? 2 : 3;  // log2 of the element size
+  const int64_t pa = s.lda << sh, po = s.n << sh;
+  const GlobalT<char>* A = (const GlobalT<char>*)s.A + (t0 << sh);
+  GlobalT<char>* L = (GlobalT<char>*)s.lambda + (t0 << sh);
+  GlobalT<char>* W = (GlobalT<char>*)s.V + (t0 << sh);
+  const bool vecs = s.V != nullptr;
+  uint32_t off = threadIdx.x << sh;
+  asm volatile("" : "+v"(off));
+  double a[6];
+  if (f32) load_planes<float>(a, A, pa, off);
+  else load_planes<double>(a, A, pa, off);
+  double l[3], v[9];
+  bool bad;
+  solve3<true, kFormBoth>(a, s.flags, l, v, bad);
+  if (bad) {  // a NaN or infinite entry: NaN in every output of the matrix
+#pragma unroll
+    for (int j = 0; j < 3; ++j) l[j] = qnan<double>();
+#pragma unroll
+    for (int k = 0; k < 9; ++k) v[k] = qnan<double>();
+  }
+  uint32_t soff = off;
+  asm volatile("" : "+v"(soff));
+  if (f32) {
+    store_planes<float>(l, L, po, soff);
+    if (vecs) store_planes<float>(v, W, po, soff);
+  } else {
+    store_planes<double>(l, L, po, soff);
+    if (vecs) store_planes<double>(v, W, po, soff);
+  }
+}
+
+// The chunked order from here on: 4096 tiles, 200 stress-mix requests of
+// 2^U(0,20) matrices (57 K tiles, planes mostly unaligned) 349 us against 367
+// in launch order; 1024 requests of 2^U(0,10) (1364 tiles) 9.1 against 8.4.
+constexpr int64_t kSegmentsChunkFrom = 4096;
+
+// begin: the segments' first tiles, ascending; LOADS of them per lane and
+// round of the search.
+template <int LOADS, typename Begins, typename Segments>
+__device__ __forceinline__ void solve_segments(int nseg, int64_t total_tiles, Begins begin,
+                                               Segments seg) {
+  // A tile's segment is the last whose first tile is at or before it
+  // (uniform across the workgroup).  Its index is the count of segments
+  // starting at or before the tile, minus one: each lane tests LOADS segments
+  // and ballots count them, kRound per round, with the loads in flight
+  // together.  A round not all of whose segments start at or before the tile
+  // is the last.  A workgroup's tiles ascend, so its next search starts at
+  // the round that held this tile's segment.
+  constexpr int kRound = LOADS * kWave;
+  // with one workgroup per tile, neighbouring tiles on one XCD
+  Order order{0, 5};
+  if (total_tiles >= kSegmentsChunkFrom && total_tiles <= (int64_t)gridDim.x)
+    order.chunked = (uint32_t)total_tiles / (kXcds << 5) * (kXcds << 5);
   int from = 0;  // a multiple of kRound; every segment before it qualifies
-  for (int64_t tile = blockIdx.x; tile < total_tiles; tile += gridDim.x) {
+  for (int64_t slot = blockIdx.x; slot < total_tiles; slot += gridDim.x) {
+    const int64_t tile = order.chunked ? (int64_t)tile_of_block((uint32_t)slot, order) : slot;
     int cnt = from;
     for (int base = from; base < nseg; base += kRound) {
-      int64_t tb[4];
+      int64_t tb[LOADS];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
+      for (int u = 0; u < LOADS; ++u) {
         const int j = base + u * kWave + (int)(threadIdx.x % kWave);
-        tb[u] = j < nseg ? t->seg[j].tile_begin : INT64_MAX;
+        tb[u] = j < nseg ? begin[j] : INT64_MAX;
       }
       int c = 0;
 #pragma unroll
-      for (int u = 0; u < 4; ++u) c += __popcll(__ballot(tb[u] <= tile));
+      for (int u = 0; u < LOADS; ++u) c += __popcll(__ballot(tb[u] <= tile));
       cnt += c;
       if (c < kRound) break;
     }
     const int lo = cnt - 1;
     from = lo / kRound * kRound;
-    const Segment s = t->seg[lo];
+    Segment s;
+    s.A = seg[lo].A;
+    s.lambda = seg[lo].lambda;
+    s.V = seg[lo].V;
+    s.n = seg[lo].n;
+    s.lda = seg[lo].lda;
+    s.tile_begin = seg[lo].tile_begin;
+    s.dtype = seg[lo].dtype;
+    s.flags = seg[lo].flags;
     const int64_t t0 = (tile - s.tile_begin) * kBlock;  // the tile's first matrix
-    if (t0 + threadIdx.x < s.n) {
-      // the server admits the FP64 and the refined FP32 form
-      if (s.dtype == kFormF64) solve_segment_tile<kFormF64>(s, t0);
-      else solve_segment_tile<kFormF32R>(s, t0);
-    }
+    // the server admits the FP64 and the refined FP32 form
+    if (t0 + threadIdx.x < s.n) solve_segment_tile(s, t0);
   }
+}
+
+__global__ __launch_bounds__(kBlock) void k_syev3_segments(const TickTable* __restrict__ t) {
+  solve_segments<4>(t->nseg, t->total_tiles, table_begins(t), t->seg);
+}
+
+// The table is the kernel's argument, read where the launch put it (indexed
+// as a parameter it could be copied to scratch memory).
+__global__ __launch_bounds__(kBlock) void k_syev3_segments_inline(InlineTable) {
+  using Arg = const __attribute__((address_space(4))) InlineTable;
+  Arg* t = (Arg*)__builtin_amdgcn_kernarg_segment_ptr();
+  solve_segments<1>(t->nseg, t->total_tiles, t->begin, t->seg);
 }
 
 hipError_t launch_segments(const TickTable* table, int32_t grid_blocks,
                            hipStream_t stream) {
   hipLaunchKernelGGL(k_syev3_segments, dim3((unsigned)grid_blocks), dim3(kBlock), 0,
+                     stream, table);
+  return hipGetLastError();
+}
+
+hipError_t launch_segments_inline(const InlineTable& table, int32_t grid_blocks,
+                                  hipStream_t stream) {
+  hipLaunchKernelGGL(k_syev3_segments_inline, dim3((unsigned)grid_blocks), dim3(kBlock), 0,
                      stream, table);
   return hipGetLastError();
 }

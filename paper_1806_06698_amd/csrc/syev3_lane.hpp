@@ -60,6 +60,9 @@ constexpr uint32_t kFlagNoScale = 32u;
 constexpr int kFormF64 = 0;
 constexpr int kFormF32R = 1;
 constexpr int kFormF32 = 2;
+// FP64 or FP32 storage with FP64 refinement, told apart by the caller's
+// loads and stores alone: the serving kernel, which meets both.
+constexpr int kFormBoth = 3;
 
 enum Branch : int { kZero = 0, kNonFinite = 1, kDiagonal = 2, kDeflated = 3,
                     kReduced = 4 };
@@ -873,18 +876,19 @@ __device__ __forceinline__ int solve3(const double (&ain)[6], uint32_t flags,
         mu = (double)y1;
         nu = (double)y2;
       }
-    } else if (FORM == kFormF32R) {
-      zeros_bg(al, be1, be2, g1, g2, hh, flags & kFlagRefineConverge, mu, nu, it1, it2);
-      it1 += 2;  // and the two FP32 steps of the start
-      it2 += 2;
-    } else if (flags & kFlagNewton) {
+    } else if (FORM != kFormF32R && (flags & kFlagNewton)) {
       const Arrows P = arrows(al, be1, be2, g1, g2);
       zeros_newton(P.mu, P.nu, mu, nu, it1, it2);
-    } else if (flags & kFlagPaperBG) {
+    } else if (FORM != kFormF32R && (flags & kFlagPaperBG)) {
       const Arrows P = arrows(al, be1, be2, g1, g2);
       zeros_bg_paper(P.mu, P.nu, mu, nu, it1, it2);
     } else {
-      zeros_bg(al, be1, be2, g1, g2, hh, false, mu, nu, it1, it2);
+      zeros_bg(al, be1, be2, g1, g2, hh, FORM != kFormF64 && (flags & kFlagRefineConverge), mu,
+               nu, it1, it2);
+      if (FORM == kFormF32R) {  // and the two FP32 steps of the start
+        it1 += 2;
+        it2 += 2;
+      }
     }
     // lambda3 <= lambda2 <= lambda1; lambda2 by the trace identity
     l2 = __builtin_fma(mu, unscale, al1);

@@ -170,6 +170,7 @@ Request* lookup(syev3_server* s, int64_t id, int* slot_out) {
 int syev3_server::launch_tick(int slot) {
   TickSlot& tk = ticks[slot];
   syev3::TickTable* t = tk.h_table;
+  int64_t* begins = syev3::table_begins(t);
   int nseg = 0;
   int64_t tiles = 0;
   bool staged_out = false;
@@ -180,6 +181,7 @@ int syev3_server::launch_tick(int slot) {
     const int ri = queue.front();
     queue.pop_front();
     Request& r = req[ri];
+    begins[nseg] = tiles;
     syev3::Segment& sg = t->seg[nseg++];
     sg.A = r.A;
     sg.lambda = r.lam;
@@ -358,6 +360,7 @@ int syev3_server::init(const syev3_server_opts& opts) {
         hipMalloc((void**)&tk.d_table, table_bytes) != hipSuccess)
       return SYEV3_E_HIP;
     std::memset(tk.h_table, 0, table_bytes);
+    tk.h_table->cap = o.max_segments_per_tick;
     if (o.use_graphs) {
       // capture: table copy, then the segment kernel; replayed per tick
       bool ok = hipStreamBeginCapture(tk.stream, hipStreamCaptureModeThreadLocal) == hipSuccess;
