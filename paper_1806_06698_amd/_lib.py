@@ -10,6 +10,7 @@ import os
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "libsyev3.so")
+BINDING_PATH = os.path.join(_PKG, "_binding.so")
 
 F64 = 0
 F32_REFINE = 1
@@ -41,6 +42,7 @@ class Syev3Error(RuntimeError):
 
 
 _lib = None
+_binding = None
 
 
 class ServerOpts(ctypes.Structure):
@@ -132,6 +134,20 @@ def lib() -> ctypes.CDLL:
         L.syev3_server_get_stats.restype = i32
     _lib = L
     return L
+
+
+def binding():
+    """The native fast paths of this package's calls (csrc/syev3_binding.cpp;
+    raises if it is not built)."""
+    global _binding
+    if _binding is None:
+        lib()
+        if not os.path.exists(BINDING_PATH):
+            raise RuntimeError(
+                f"{BINDING_PATH} is missing: build it with `python -m paper_1806_06698_amd.build`")
+        from . import _binding as module
+        _binding = module
+    return _binding
 
 
 def strerror(code: int) -> str:

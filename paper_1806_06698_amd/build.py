@@ -1,9 +1,12 @@
-"""Build libsyev3.so (HIP, gfx950) in-tree with hipcc.
+"""Build libsyev3.so (HIP, gfx950) in-tree with hipcc, and the Python
+binding's native part with the host compiler.
 
     python -m paper_1806_06698_amd.build
 
-compiles every source under csrc/ into paper_1806_06698_amd/libsyev3.so.
-hipcc cross-compiles for gfx950 without a GPU present.
+compiles the library's sources under csrc/ into
+paper_1806_06698_amd/libsyev3.so, and syev3_binding.cpp, which needs torch's
+headers, into paper_1806_06698_amd/_binding.so.  hipcc cross-compiles for
+gfx950 without a GPU present.
 """
 from __future__ import annotations
 
@@ -11,6 +14,7 @@ import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 import tempfile
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -18,6 +22,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libsyev3.so")
+BINDING = os.path.join(PKG, "_binding.so")
 
 SOURCES = ["syev3_kernels.hip", "syev3_noalloc.hip", "syev3_api.cpp", "syev3_server.cpp"]
 
@@ -72,7 +77,33 @@ def build(verbose: bool = False) -> str:
             print(" ".join(cmd), flush=True)
         subprocess.run(cmd, check=True)
         os.replace(out_tmp, LIB)
+    build_binding(cc, verbose)
     return LIB
+
+
+def build_binding(cc: str, verbose: bool = False) -> str:
+    """Compile the binding (host code only) against the library just built."""
+    import torch
+    from torch.utils import cpp_extension
+
+    rocm = os.path.dirname(os.path.dirname(os.path.realpath(cc)))
+    torch_lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    out_tmp = BINDING + ".tmp"
+    cmd = [shutil.which("g++") or "c++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+           "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-I", INCLUDE, *[a for d in cpp_extension.include_paths() for a in ("-isystem", d)],
+           "-isystem", os.path.join(rocm, "include"),
+           "-isystem", sysconfig.get_paths()["include"],
+           os.path.join(CSRC, "syev3_binding.cpp"), "-o", out_tmp,
+           "-L" + torch_lib, "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip",
+           "-L" + PKG, "-l:" + os.path.basename(LIB), "-Wl,-rpath,$ORIGIN",
+           "-Wl,-rpath," + torch_lib]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    os.replace(out_tmp, BINDING)
+    return BINDING
 
 
 if __name__ == "__main__":

@@ -102,14 +102,34 @@ class Request:
     def __init__(self, server, rid, bufs: RequestBuffers, dtype, A=None):
         self.server, self.id, self.n = server, rid, bufs.n
         self.dtype = bufs.dtype
-        tdt = torch.float64 if bufs.dtype == _lib.F64 else torch.float32
-        es = 8 if tdt == torch.float64 else 4
-        dev = server.device
+        self._bufs = bufs
         # a view's input: the caller's tensor, held until release
-        self.A = A if A is not None else _tensor_at(bufs.A, (6, bufs.n), tdt, es, dev)
-        self.lam = _tensor_at(bufs.lam, (3, bufs.n), tdt, es, dev)
-        self.V = _tensor_at(bufs.V, (9, bufs.n), tdt, es, dev) if bufs.V else None
+        self._A, self._lam, self._V = A, None, None
         self.host_buffers = None  # held from a host-staged submit to release
+
+    def _tensor(self, ptr, rows):
+        f64 = self.dtype == _lib.F64
+        return _tensor_at(ptr, (rows, self.n), torch.float64 if f64 else torch.float32,
+                          8 if f64 else 4, self.server.device)
+
+    # the tensors are made when asked for: a host-staged request needs none
+    @property
+    def A(self):
+        if self._A is None:
+            self._A = self._tensor(self._bufs.A, 6)
+        return self._A
+
+    @property
+    def lam(self):
+        if self._lam is None:
+            self._lam = self._tensor(self._bufs.lam, 3)
+        return self._lam
+
+    @property
+    def V(self):
+        if self._V is None and self._bufs.V:
+            self._V = self._tensor(self._bufs.V, 9)
+        return self._V
 
 
 def _tensor_at(ptr, shape, dtype, esize, dev):
