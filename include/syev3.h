@@ -357,14 +357,17 @@ int64_t syev3_server_acquire_view(syev3_server* s, int64_t n, int dtype,
 int syev3_server_submit(syev3_server* s, int64_t request, hipEvent_t ready);
 
 /* Host-staged submission (not for a request admitted as a view, which gives
- * SYEV3_E_STATE): the request's input is copied from host memory
- * host_A (6 planes of n, SoA, the request's dtype) to its device buffer
- * before its tick, and the outputs are copied back to host_lambda (3 x n)
- * and host_V (9 x n, or NULL) after it.  The copies run in order on the
- * tick's own stream, before and after its kernel; ticks run on separate
- * streams, so one tick's copies overlap other ticks' kernels.  The host memory must stay valid and untouched until
- * the request completes; it should be pinned (hipHostMalloc), otherwise the
- * copies do not overlap.  Completion (poll/wait) includes the copy back. */
+ * SYEV3_E_STATE): the request's input comes from host memory host_A (6 planes
+ * of n, SoA, the request's dtype) and the outputs go to host_lambda (3 x n)
+ * and host_V (9 x n, or NULL); its device buffers hold the same afterwards.
+ * In pinned memory (hipHostMalloc, not hipHostMallocNonCoherent; every buffer
+ * within one allocation, aligned to its type, and sharing no byte with another
+ * of the three) the request's tick reads and writes the buffers in place, both
+ * directions at once.  Otherwise the tick copies the input in before its
+ * kernel and the outputs back after it, in order on its own stream; copies
+ * of pageable memory do not overlap other work.  The host memory must stay
+ * valid and untouched until the request completes.  Completion (poll/wait)
+ * includes the outputs in host memory. */
 int syev3_server_submit_host(syev3_server* s, int64_t request, const void* host_A,
                              void* host_lambda, void* host_V);
 

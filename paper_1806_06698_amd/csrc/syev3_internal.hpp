@@ -81,7 +81,25 @@ struct InlineTable {
 hipError_t launch_segments_inline(const InlineTable& table, int32_t grid_blocks,
                                   hipStream_t stream);
 
-// The same for host_table (nseg segments, total_tiles > 0; its cap and what
+// A request whose input and results are the caller's pinned host memory, in
+// planes of n: its matrices are read from there and also stored to s.A, its
+// results stored to s.lambda and s.V and, where not NULL, to lambda and V.
+struct HostSegment {
+  Segment s;  // s.lda == s.n
+  const void* A;
+  void* lambda;
+  void* V;
+};
+constexpr int kHostSegments = 40;
+struct HostTable {
+  int32_t nseg;
+  int64_t total_tiles;
+  int64_t begin[kHostSegments];
+  HostSegment seg[kHostSegments];
+};
+hipError_t launch_segments_host(const HostTable& table, hipStream_t stream);
+
+// launch_segments for host_table (nseg segments, total_tiles > 0; its cap and what
 // follows the segments are not read) with no allocation: as the kernel's
 // argument up to kInlineSegments segments, else copied into the library's
 // fixed table of the stream's device.  That copy is from pageable host

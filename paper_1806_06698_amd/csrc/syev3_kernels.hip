@@ -11,6 +11,7 @@
 //     LDS the same way, so global stores are unit-stride as well.
 // Streams are read and written once; how (workgroup order, non-temporal
 // hints, workgroups per compute unit) is chosen per launch, in motion().
+#include <algorithm>
 #include <type_traits>
 
 #include "syev3_internal.hpp"
@@ -507,7 +508,30 @@ __device__ __forceinline__ void store_planes(const double (&x)[N], GlobalT<char>
   }
 }
 
-__device__ __forceinline__ void solve_segment_tile(const Segment& s, int64_t t0) {
+// A host segment's matrices: loaded from its planes in host memory and
+// stored, bit for bit, to its planes in device memory.
+template <typename T>
+__device__ __forceinline__ void load_host_planes(double (&a)[6], const GlobalT<char>* host,
+                                                 GlobalT<char>* base, int64_t pitch,
+                                                 uint32_t off) {
+  T raw[6];
+#pragma unroll
+  for (int k = 0; k < 6; ++k) raw[k] = *(const GlobalT<T>*)(host + k * pitch + off);
+#pragma unroll
+  for (int k = 0; k < 6; ++k) *(GlobalT<T>*)(base + k * pitch + off) = raw[k];
+#pragma unroll
+  for (int k = 0; k < 6; ++k) a[k] = (double)raw[k];
+}
+
+// The host memory of a segment that has any.
+struct HostSide {
+  const void* A;
+  void *lambda, *V;
+};
+
+template <bool HOST>
+__device__ __forceinline__ void solve_segment_tile(const Segment& s, const HostSide& h,
+                                                   int64_t t0) {
   const bool f32 = s.dtype != kFormF64;
   const int sh = f32 ? 2 : 3;  // log2 of the element size
   const int64_t pa = s.lda << sh, po = s.n << sh;
@@ -518,8 +542,14 @@ __device__ __forceinline__ void solve_segment_tile(const Segment& s, int64_t t0)
   uint32_t off = threadIdx.x << sh;
   asm volatile("" : "+v"(off));
   double a[6];
-  if (f32) load_planes<float>(a, A, pa, off);
-  else load_planes<double>(a, A, pa, off);
+  if constexpr (HOST) {
+    const GlobalT<char>* hA = (const GlobalT<char>*)h.A + (t0 << sh);
+    if (f32) load_host_planes<float>(a, hA, (GlobalT<char>*)A, pa, off);
+    else load_host_planes<double>(a, hA, (GlobalT<char>*)A, pa, off);
+  } else {
+    if (f32) load_planes<float>(a, A, pa, off);
+    else load_planes<double>(a, A, pa, off);
+  }
   double l[3], v[9];
   bool bad;
   solve3<true, kFormBoth>(a, s.flags, l, v, bad);
@@ -531,13 +561,19 @@ __device__ __forceinline__ void solve_segment_tile(const Segment& s, int64_t t0)
   }
   uint32_t soff = off;
   asm volatile("" : "+v"(soff));
-  if (f32) {
-    store_planes<float>(l, L, po, soff);
-    if (vecs) store_planes<float>(v, W, po, soff);
-  } else {
-    store_planes<double>(l, L, po, soff);
-    if (vecs) store_planes<double>(v, W, po, soff);
-  }
+  const auto store = [&](GlobalT<char>* lam, GlobalT<char>* vec, bool with_vec) {
+    if (f32) {
+      store_planes<float>(l, lam, po, soff);
+      if (with_vec) store_planes<float>(v, vec, po, soff);
+    } else {
+      store_planes<double>(l, lam, po, soff);
+      if (with_vec) store_planes<double>(v, vec, po, soff);
+    }
+  };
+  if constexpr (HOST)
+    store((GlobalT<char>*)h.lambda + (t0 << sh), (GlobalT<char>*)h.V + (t0 << sh),
+          h.V != nullptr);
+  store(L, W, vecs);
 }
 
 // The chunked order from here on: 4096 tiles, 200 stress-mix requests of
@@ -546,10 +582,10 @@ __device__ __forceinline__ void solve_segment_tile(const Segment& s, int64_t t0)
 constexpr int64_t kSegmentsChunkFrom = 4096;
 
 // begin: the segments' first tiles, ascending; LOADS of them per lane and
-// round of the search.
-template <int LOADS, typename Begins, typename Segments>
+// round of the search.  solve(i, tile): solves this tile of segment i.
+template <int LOADS, typename Begins, typename Solve>
 __device__ __forceinline__ void solve_segments(int nseg, int64_t total_tiles, Begins begin,
-                                               Segments seg) {
+                                               Solve solve) {
   // A tile's segment is the last whose first tile is at or before it
   // (uniform across the workgroup).  Its index is the count of segments
   // starting at or before the tile, minus one: each lane tests LOADS segments
@@ -581,23 +617,37 @@ __device__ __forceinline__ void solve_segments(int nseg, int64_t total_tiles, Be
     }
     const int lo = cnt - 1;
     from = lo / kRound * kRound;
-    Segment s;
-    s.A = seg[lo].A;
-    s.lambda = seg[lo].lambda;
-    s.V = seg[lo].V;
-    s.n = seg[lo].n;
-    s.lda = seg[lo].lda;
-    s.tile_begin = seg[lo].tile_begin;
-    s.dtype = seg[lo].dtype;
-    s.flags = seg[lo].flags;
-    const int64_t t0 = (tile - s.tile_begin) * kBlock;  // the tile's first matrix
-    // the server admits the FP64 and the refined FP32 form
-    if (t0 + threadIdx.x < s.n) solve_segment_tile(s, t0);
+    solve(lo, tile);
   }
 }
 
+// A table's segment, field by field (in scalar registers).
+template <typename Seg>
+__device__ __forceinline__ Segment read_segment(Seg* g) {
+  Segment s;
+  s.A = g->A;
+  s.lambda = g->lambda;
+  s.V = g->V;
+  s.n = g->n;
+  s.lda = g->lda;
+  s.tile_begin = g->tile_begin;
+  s.dtype = g->dtype;
+  s.flags = g->flags;
+  return s;
+}
+
+// The server admits the FP64 and the refined FP32 form.
+template <bool HOST>
+__device__ __forceinline__ void solve_tile_of(const Segment& s, const HostSide& h,
+                                              int64_t tile) {
+  const int64_t t0 = (tile - s.tile_begin) * kBlock;  // the tile's first matrix
+  if (t0 + threadIdx.x < s.n) solve_segment_tile<HOST>(s, h, t0);
+}
+
 __global__ __launch_bounds__(kBlock) void k_syev3_segments(const TickTable* __restrict__ t) {
-  solve_segments<4>(t->nseg, t->total_tiles, table_begins(t), t->seg);
+  solve_segments<4>(t->nseg, t->total_tiles, table_begins(t), [&](int i, int64_t tile) {
+    solve_tile_of<false>(read_segment(&t->seg[i]), HostSide{}, tile);
+  });
 }
 
 // The table is the kernel's argument, read where the launch put it (indexed
@@ -605,7 +655,29 @@ __global__ __launch_bounds__(kBlock) void k_syev3_segments(const TickTable* __re
 __global__ __launch_bounds__(kBlock) void k_syev3_segments_inline(InlineTable) {
   using Arg = const __attribute__((address_space(4))) InlineTable;
   Arg* t = (Arg*)__builtin_amdgcn_kernarg_segment_ptr();
-  solve_segments<1>(t->nseg, t->total_tiles, t->begin, t->seg);
+  solve_segments<1>(t->nseg, t->total_tiles, t->begin, [&](int i, int64_t tile) {
+    solve_tile_of<false>(read_segment(&t->seg[i]), HostSide{}, tile);
+  });
+}
+
+// Bound by the host link, whose two directions run at once: one FP64 request
+// of 400 K matrices with vectors, 38 MB back, 784 us (49 GB/s; a large copy
+// alone reaches 57) against 1116 for a copy in, the solve and two copies
+// back; 100 matrices 29 us against 66.  Few workgroups keep the link full,
+// and the other compute units free for other ticks' kernels: 2^21 matrices
+// 3830 us with 32 of them, 3826 with 128, 3872 with 512, 3976 with 2048;
+// 400 K 784, 791, 837, 911.
+constexpr int kHostBlocks = 64;
+
+__global__ __launch_bounds__(kBlock) void k_syev3_segments_host(HostTable) {
+  using Arg = const __attribute__((address_space(4))) HostTable;
+  Arg* t = (Arg*)__builtin_amdgcn_kernarg_segment_ptr();
+  // whatever these caches hold of the host's memory may be out of date
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "");
+  solve_segments<1>(t->nseg, t->total_tiles, t->begin, [&](int i, int64_t tile) {
+    const HostSide h{t->seg[i].A, t->seg[i].lambda, t->seg[i].V};
+    solve_tile_of<true>(read_segment(&t->seg[i].s), h, tile);
+  });
 }
 
 hipError_t launch_segments(const TickTable* table, int32_t grid_blocks,
@@ -619,6 +691,14 @@ hipError_t launch_segments_inline(const InlineTable& table, int32_t grid_blocks,
                                   hipStream_t stream) {
   hipLaunchKernelGGL(k_syev3_segments_inline, dim3((unsigned)grid_blocks), dim3(kBlock), 0,
                      stream, table);
+  return hipGetLastError();
+}
+
+hipError_t launch_segments_host(const HostTable& table, hipStream_t stream) {
+  const int64_t grid = std::min<int64_t>(table.total_tiles, kHostBlocks);
+  (void)hipGetLastError();  // read below: drop any stale error
+  hipLaunchKernelGGL(k_syev3_segments_host, dim3((unsigned)grid), dim3(kBlock), 0, stream,
+                     table);
   return hipGetLastError();
 }
 

@@ -8,7 +8,9 @@
 // one of `max_inflight_ticks` streams: the copy of the table to the device,
 // then the segment kernel with one workgroup per tile of the tick, issued
 // directly or (use_graphs) as a graph captured once per tick slot whose
-// kernel node's grid is set before each replay.  While some ticks
+// kernel node's grid is set before each replay.  Host-staged requests whose
+// buffers are pinned are solved by a kernel that reads and writes them in
+// place; others are copied in and out by the tick.  While some ticks
 // run, newly submitted requests go into the next free slot's tick, so work
 // of different ticks overlaps on the device.  Completion is observed by
 // polling each tick's event; results are then readable and the request can
@@ -75,13 +77,16 @@ struct Request {
   const void* h_A = nullptr;
   void* h_lam = nullptr;
   void* h_V = nullptr;
+  bool direct = false;  // the kernel reads and writes the host memory itself
   Clock::time_point t_submit, t_done;
 };
 
 struct TickSlot {
-  // A tick runs in order on its own stream: the host-staged inputs' copies,
-  // the table copy and the kernel, the copies of host-staged results, then
-  // its completion event.  Ticks overlap one another (one tick's copies with
+  // A tick runs in order on its own stream: the copies of pageable
+  // host-staged inputs, the kernel on pinned host memory, the table copy and
+  // the segment kernel, the copies of pageable results, then its completion
+  // event (recorded with a system-scope release: what the kernel wrote to
+  // host memory is there once the event has completed).  Ticks overlap one another (one tick's copies with
   // another's kernel) because each slot has its own stream.  Copy streams of
   // their own per slot had only multiplied the streams sharing the process's
   // few hardware queues: host-staged throughput at 4 slots was about half of
@@ -96,6 +101,7 @@ struct TickSlot {
   hipGraphNode_t knode = nullptr;
   hipKernelNodeParams kparams{};
   int32_t grid_set = 0;  // the grid the instantiated graph launches now
+  syev3::HostTable h_host{};  // the tick's direct host-staged requests
   std::vector<int> reqs;
   bool busy = false;
   // a profiler range from launch to observed completion
@@ -165,6 +171,41 @@ Request* lookup(syev3_server* s, int64_t id, int* slot_out) {
   return r;
 }
 
+// The address range [p, p + bytes) lies in one pinned host allocation that
+// the device reaches at the same address and keeps coherent.
+bool device_reaches(int device, const void* p, size_t bytes) {
+  hipPointerAttribute_t at{};
+  void* base = nullptr;
+  size_t size = 0;
+  if (hipPointerGetAttributes(&at, p) != hipSuccess || at.type != hipMemoryTypeHost ||
+      at.devicePointer != p || at.isManaged || (at.allocationFlags & hipHostMallocNonCoherent) ||
+      (at.device != device && !(at.allocationFlags & hipHostMallocPortable)) ||
+      hipMemGetAddressRange((hipDeviceptr_t*)&base, &size, (hipDeviceptr_t)p) != hipSuccess) {
+    (void)hipGetLastError();  // pageable memory is no error here
+    return false;
+  }
+  const uintptr_t off = (uintptr_t)p - (uintptr_t)base;
+  return off <= size && bytes <= size - off;
+}
+
+bool overlap(const void* a, size_t na, const void* b, size_t nb) {
+  return (uintptr_t)a < (uintptr_t)b + nb && (uintptr_t)b < (uintptr_t)a + na;
+}
+
+// Whether the kernel may take a host-staged request's buffers as they are:
+// pinned, of aligned values, and no result's memory shared with the input's
+// or another result's (copies finish reading before the results are
+// written, and write the vectors last).
+bool takes_direct(int device, const Request& r, const void* A, void* lam, void* V) {
+  const size_t es = r.dtype == SYEV3_F64 ? 8 : 4;
+  const size_t plane = (size_t)r.n * es, bA = 6 * plane, bl = 3 * plane, bV = V ? 9 * plane : 0;
+  if (((uintptr_t)A | (uintptr_t)lam | (uintptr_t)V) % es) return false;
+  if (overlap(A, bA, lam, bl) || (V && (overlap(A, bA, V, bV) || overlap(lam, bl, V, bV))))
+    return false;
+  return device_reaches(device, A, bA) && device_reaches(device, lam, bl) &&
+         (!V || device_reaches(device, V, bV));
+}
+
 }  // namespace
 
 int syev3_server::launch_tick(int slot) {
@@ -173,27 +214,45 @@ int syev3_server::launch_tick(int slot) {
   int64_t* begins = syev3::table_begins(t);
   int nseg = 0;
   int64_t tiles = 0;
+  // direct host-staged requests: as many launches as their tables take
+  syev3::HostTable& ht = tk.h_host;
+  ht.nseg = 0;
+  ht.total_tiles = 0;
   bool staged_out = false;
   hipError_t e = hipSuccess;
   hipEvent_t last_ready = nullptr;
   tk.reqs.clear();
-  while (!queue.empty() && nseg < o.max_segments_per_tick) {
+  while (!queue.empty() && (int)tk.reqs.size() < o.max_segments_per_tick) {
     const int ri = queue.front();
     queue.pop_front();
     Request& r = req[ri];
-    begins[nseg] = tiles;
-    syev3::Segment& sg = t->seg[nseg++];
+    const int64_t first = r.direct ? ht.total_tiles : tiles;
+    (r.direct ? ht.begin[ht.nseg] : begins[nseg]) = first;
+    syev3::Segment& sg = r.direct ? ht.seg[ht.nseg].s : t->seg[nseg];
     sg.A = r.A;
     sg.lambda = r.lam;
     sg.V = r.vecs ? r.V : nullptr;
     sg.n = r.n;
     sg.lda = r.lda;
-    sg.tile_begin = tiles;
+    sg.tile_begin = first;
     sg.dtype = r.dtype;
     sg.flags = 0;
-    tiles += (r.n + syev3::kBlock - 1) / syev3::kBlock;
+    (r.direct ? ht.total_tiles : tiles) += (r.n + syev3::kBlock - 1) / syev3::kBlock;
     r.state = kRunning;
     tk.reqs.push_back(ri);
+    if (r.direct) {
+      syev3::HostSegment& hs = ht.seg[ht.nseg];
+      hs.A = r.h_A;
+      hs.lambda = r.h_lam;
+      hs.V = r.h_V;
+      if (++ht.nseg == syev3::kHostSegments) {
+        if (e == hipSuccess) e = syev3::launch_segments_host(ht, tk.stream);
+        ht.nseg = 0;
+        ht.total_tiles = 0;
+      }
+      continue;
+    }
+    ++nseg;
     // requests submitted together often share one ready event: wait once.
     // A wait that cannot be enqueued fails the tick: its input may not be
     // complete.
@@ -207,9 +266,10 @@ int syev3_server::launch_tick(int slot) {
     }
     if (r.h_lam) staged_out = true;
   }
+  if (ht.nseg > 0 && e == hipSuccess) e = syev3::launch_segments_host(ht, tk.stream);
   t->nseg = nseg;
   t->total_tiles = tiles;
-  if (e == hipSuccess) {
+  if (nseg > 0 && e == hipSuccess) {
     const int32_t grid = tick_grid(tiles);
     if (tk.exec) {
       // the slot's previous tick has completed, so its graph may be changed
@@ -230,7 +290,7 @@ int syev3_server::launch_tick(int slot) {
     // results back to the host; the tick completes after them
     for (int ri : tk.reqs) {
       const Request& r = req[ri];
-      if (!r.h_lam || e != hipSuccess) continue;
+      if (!r.h_lam || r.direct || e != hipSuccess) continue;
       const size_t es = r.dtype == SYEV3_F64 ? 8 : 4;
       e = hipMemcpyAsync(r.h_lam, r.lam, 3 * (size_t)r.n * es, hipMemcpyDeviceToHost,
                          tk.stream);
@@ -246,7 +306,7 @@ int syev3_server::launch_tick(int slot) {
   if (busy_ticks++ == 0) busy_since = Clock::now();
   st.ticks++;
   st.inflight_ticks_peak = std::max(st.inflight_ticks_peak, busy_ticks);
-  st.segments_per_tick_peak = std::max(st.segments_per_tick_peak, nseg);
+  st.segments_per_tick_peak = std::max(st.segments_per_tick_peak, (int32_t)tk.reqs.size());
   return SYEV3_OK;
 }
 
@@ -443,6 +503,7 @@ int64_t admit(syev3_server* s, int64_t n, int dtype, int want_vectors, const voi
   r.h_A = nullptr;
   r.h_lam = nullptr;
   r.h_V = nullptr;
+  r.direct = false;
   s->st.pool_bytes_in_use = s->alloc->in_use();
   s->st.pool_bytes_peak = std::max<uint64_t>(s->st.pool_bytes_peak, s->alloc->in_use());
   bufs->A = const_cast<void*>(r.A);
@@ -598,6 +659,7 @@ int syev3_server_submit_host(syev3_server* s, int64_t id, const void* host_A,
     r->h_A = host_A;
     r->h_lam = host_lambda;
     r->h_V = r->vecs ? host_V : nullptr;
+    r->direct = takes_direct(s->device, *r, r->h_A, r->h_lam, r->h_V);
     r->t_submit = Clock::now();
     s->note_queue();
     s->st.submitted++;

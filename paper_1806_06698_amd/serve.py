@@ -228,13 +228,14 @@ class Server:
 
     def submit_host(self, req: Request, host_A, host_lam, host_V=None):
         """Host-staged submission: host_A (6, n), host_lam (3, n), host_V
-        (9, n) are CPU tensors of the request's dtype, preferably pinned; the
-        server copies A in before the tick and the results out after it."""
+        (9, n) are CPU tensors of the request's dtype.  The request's tick
+        reads and writes pinned ones in place; it copies pageable ones (and
+        any that share memory) in before its kernel and out after it."""
         check_host_buffers(req.n, req.dtype, host_A, host_lam, host_V)
         _lib.check(self.L.syev3_server_submit_host(
             self.h, req.id, host_A.data_ptr(), host_lam.data_ptr(),
             host_V.data_ptr() if host_V is not None else None), "syev3_server_submit_host")
-        # the copies run when the tick does: keep the buffers alive till release
+        # the tick uses them when it runs: keep the buffers alive till release
         req.host_buffers = (host_A, host_lam, host_V)
 
     def poll(self, req):
