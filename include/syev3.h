@@ -69,20 +69,18 @@ extern "C" {
 
 /* dtypes */
 #define SYEV3_F64 0          /* FP64 storage, FP64 arithmetic */
-#define SYEV3_F32_REFINE 1   /* FP32 storage; FP64 reduction, deflation test
-                                and eigenvectors.  Each root: an FP32 start
-                                and one FP32 Borges-Gragg step, then an FP64
-                                Newton step (Sec. 1.4.2), a second one where
-                                the first moved it by more than 2^-22 of
-                                itself, and FP64 Borges-Gragg steps where it
-                                moved it by more than 2^-14.  Eigenvalues
-                                within eps32 ||A|| / 16 of the exact ones
-                                before rounding to FP32 */
+#define SYEV3_F32_REFINE 1   /* FP32 storage; the solve is SYEV3_F64's:
+                                each root has an FP32 start (an upper bound,
+                                a chord and two Laguerre steps) and an FP64
+                                Halley step, and FP64 steps from there on
+                                (Halley, then Borges-Gragg) where that moved
+                                it by more than 2^-17.5 of itself.
+                                Eigenvalues within eps32 ||A|| / 16 of the
+                                exact ones before rounding to FP32 */
 #define SYEV3_F32 2          /* FP32 storage without the refinement: the
                                 zeros of an FP32 Borges-Gragg iteration are
-                                used as they are and the vectors come from
-                                the formulas of Sec. 1 without
-                                re-orthogonalisation.  For measuring what
+                                used as they are, with the vectors from
+                                the same formulas.  For measuring what
                                 the refinement buys (an ablation); the
                                 server does not accept it */
 
@@ -100,7 +98,7 @@ extern "C" {
                                      literally); by default h <= eps (|alpha1|
                                      + |alpha2| + |gamma|) also is */
 #define SYEV3_FLAG_NEWTON 4u      /* Newton's method from the left
-                                     (Sec. 1.4.2) instead of Borges-Gragg;
+                                     (Sec. 1.4.2) instead of the default;
                                      SYEV3_F64 only */
 #define SYEV3_FLAG_PAPER_BG 8u    /* Borges-Gragg exactly as Sec. 1.4.1
                                      states it: start from the first iterate
@@ -108,14 +106,12 @@ extern "C" {
                                      For measuring what the default start
                                      and stop test save; SYEV3_F64 only, not
                                      with SYEV3_FLAG_NEWTON */
-#define SYEV3_FLAG_REFINE_CONVERGE 16u /* FP32 storage: after the first FP64
-                                     Newton step, continue every root with
+#define SYEV3_FLAG_REFINE_CONVERGE 16u /* FP32 storage: after the FP64
+                                     Halley step, continue every root with
                                      FP64 Borges-Gragg steps (Sec. 1.4.1)
                                      until their stop test, as is otherwise
-                                     done only when the Newton correction
-                                     exceeds 2^-14 of the root.  Eigenvalues as
-                                     accurate as the FP64 zero finder makes
-                                     them, for one or two more FP64
+                                     done only where Halley's steps leave
+                                     one unfinished: one or two more FP64
                                      evaluations per root; SYEV3_F32_REFINE
                                      only */
 #define SYEV3_FLAG_NO_SCALE 32u   /* no power-of-two scaling of each matrix
@@ -195,7 +191,9 @@ int batched_syev3_inplace(int64_t n, void* A, void* lambda, int dtype,
  * info[i] = branch | (iterations for mu) << 8 | (iterations for nu) << 16,
  * branch: 0 zero matrix, 1 non-finite input, 2 diagonal arrow (h negligible),
  * 3 deflated (Sec. 1.1), 4 ordered and reduced (Sec. 1.2); iterations are the
- * spectral-function evaluations of the zero finder (Sec. 1.4).  info is
+ * steps of the zero finder (Sec. 1.4) in FP64, each an evaluation of the
+ * spectral function or its numerator with the derivatives (for
+ * SYEV3_F32_REFINE with the two FP32 steps of the start).  info is
  * device memory of n int32 values.  Used to measure iteration counts.
  */
 int batched_syev3_info(int64_t n, const void* A, int64_t ld, int layout,
@@ -399,10 +397,11 @@ int syev3_server_get_stats(syev3_server* s, syev3_server_stats* out);
  * nseg independent requests of different sizes and forms in one launch of
  * the kernel that runs a server's ticks, on buffers the caller owns.  That
  * kernel reads a table of the requests; a server allocates one per tick
- * slot in syev3_server_create, this call uses a fixed array of the library
- * in each GPU's memory instead (room for SYEV3_SEGMENTS_MAX segments, about
- * 56 KiB, held until the process ends) and makes no hipMalloc, hipFree or
- * other allocating call.  Results are bitwise those of the same requests
+ * slot in syev3_server_create.  Here it is the launch's kernel argument for
+ * at most 56 segments with n > 0; for more, this call uses a fixed array of
+ * the library in each GPU's memory (room for SYEV3_SEGMENTS_MAX segments,
+ * about 72 KiB, held until the process ends).  It makes no hipMalloc,
+ * hipFree or other allocating call.  Results are bitwise those of the same requests
  * served by a server or solved by batched_syev3_strided.
  *
  * segs[i]: n >= 0 matrices of dtype SYEV3_F64 or SYEV3_F32_REFINE; A holds
@@ -410,13 +409,15 @@ int syev3_server_get_stats(syev3_server* s, syev3_server_stats* out);
  * 3 planes and V 9 planes (NULL: eigenvalues only) at plane stride n; flags
  * as for batched_syev3_ex.  All device memory of the stream's device.
  * Segments with n == 0 are skipped.  The table is built from segs on the
- * host and copied to the device from pageable host memory, which HIP does
- * synchronously with respect to the host: segs may be reused as soon as
- * the call returns.  The solve is enqueued on `stream`.
+ * host and travels with the launch, or is copied to the device from pageable
+ * host memory, which HIP does synchronously with respect to the host: segs
+ * may be reused as soon as the call returns.  The solve is enqueued on
+ * `stream`.
  *
- * Every call on one GPU uses that GPU's one table, which keeps the last
- * call's contents (each call writes all of the table it reads).  Calls in
- * one stream's order are safe; calls that overlap on one GPU (on streams
+ * Calls of at most 56 segments share nothing and may overlap.  Every larger
+ * call on one GPU uses that GPU's one table, which keeps the last such
+ * call's contents (each call writes all of the table it reads).  Larger calls
+ * in one stream's order are safe; ones that overlap on one GPU (on streams
  * not ordered with each other) race, and a kernel may then read a table
  * that another call has overwritten.  The table's device address
  * is looked up at the first call on each GPU and kept: after a

@@ -338,10 +338,12 @@ constexpr int64_t kManyBlocks = 3072;
 //    and, where the plane stride comes within 64 KB of a multiple of 2^29
 //    bytes, so that all planes meet the same channels at once, chunks of
 //    256 (2^26 + 4096: 1677 against 1837; 2^27: 3424 against 3543; 2^26:
-//    1626 against 1751 on one device, 1674 against 1670 on another).  The
-//    unrefined FP32 form does the same at 2^28 bytes (2^26: 908 against 961);
-//    the refined one gains nothing from it (912 against 918; 1014 against
-//    954 on another device).
+//    1626 against 1751 on one device, 1674 against 1670 on another).  FP64
+//    eigenvalues alone do the same (2^26: 761 against 820; 2^26 + 4096: 773
+//    against 825; 2^27: 1517 against 1695; 2^25, 268 MB: 410 against 370),
+//    and the unrefined FP32 form at 2^28 bytes (2^26: 908 against 961); the
+//    refined one gains nothing from it (912 against 918; 1014 against 954 on
+//    another device; eigenvalues alone 2^27: 1081 against 1080).
 template <int FORM, bool VECS>
 static Motion motion(int64_t blocks, const void* A, Strides ld, int layout, const void* lambda,
                      const void* V, uint32_t flags) {
@@ -356,16 +358,17 @@ static Motion motion(int64_t blocks, const void* A, Strides ld, int layout, cons
                                               valu ? 0 : kLdsFor3 - kAosLds<T>};
     return Motion{launch, true, 0};
   }
-  if (!VECS) return Motion{launch, true, 0};
+  const uint64_t far = FORM == kFormF64 ? 1u << 29 : 1u << 28;
+  const uint64_t off = ((uint64_t)(VECS ? ld.v : ld.a) * sizeof(T) + (1u << 16)) & (far - 1);
+  const bool aliased = FORM != kFormF32R && off <= (1u << 17);
+  if (!VECS)
+    return Motion{FORM == kFormF64 && aliased ? chunked_order(blocks, 8) : launch, true, 0};
   const uintptr_t bits = (uintptr_t)A | (uintptr_t)lambda | (uintptr_t)V |
                          (uintptr_t)(ld.a | ld.l | ld.v) * sizeof(T);
   const bool ragged = (bits & 127u) != 0;
   if (kHbmBound ? ragged || !many : ragged && many)
     return Motion{blocks >= 1280 ? chunked_order(blocks, 5) : launch, false,
                   kHbmBound && many && !valu ? kLdsFor3 : 0};
-  const uint64_t far = kHbmBound ? 1u << 29 : 1u << 28;
-  const uint64_t off = ((uint64_t)ld.v * sizeof(T) + (1u << 16)) & (far - 1);
-  const bool aliased = FORM != kFormF32R && off <= (1u << 17);
   return Motion{aliased ? chunked_order(blocks, 8) : launch, true,
                 kHbmBound && !valu ? kLdsFor3 : 0};
 }

@@ -12,9 +12,12 @@
 //   Sec. 1.2  for an ordered, reduced arrow: mu = lambda1 - alpha1 and
 //             nu = alpha2 - lambda3 as rightmost zeros of two fully reduced
 //             arrows, lambda2 from the trace identity, eigenvectors u1, u3, u2
-//   Sec. 1.4  the zeros by the Borges-Gragg iteration (rational model
-//             w0 x - sigma - w1/x, increment quadratic, start from +inf,
-//             stop when f/f' < 2 eps x), or by Newton's method from the left.
+//   Sec. 1.4  the zeros: an FP32 start and one FP64 Halley step on the
+//             numerator of f, whose bound on what is left is tested; zeros
+//             that do not pass it by the Borges-Gragg iteration (rational
+//             model w0 x - sigma - w1/x, increment quadratic).  By flag the
+//             paper's own iteration (start from +inf, stop when f/f' <
+//             2 eps x), or Newton's method from the left.
 //
 // Choices made here (the paper leaves them open):
 //   * every matrix is scaled by a power of two so that max |a_ij| is in
@@ -53,14 +56,14 @@ constexpr uint32_t kFlagRefineConverge = 16u;
 constexpr uint32_t kFlagNoScale = 32u;
 
 // Arithmetic forms of the solve, a template argument (equal to the dtype
-// codes of the interface): FP64 throughout; FP32 storage with FP64
-// refinement; FP32 storage with the FP32 zero finder's zeros used as they
-// are and no re-orthogonalisation (an ablation of the refinement).  Each
-// form is compiled on its own, so no form's kernel holds another's code.
+// codes of the interface): FP64; FP32 storage with the FP64 solve; FP32
+// storage with an FP32 zero finder's zeros used as they are (an ablation of
+// the refinement).  Each form is compiled on its own, so no form's kernel
+// holds another's code.
 constexpr int kFormF64 = 0;
 constexpr int kFormF32R = 1;
 constexpr int kFormF32 = 2;
-// FP64 or FP32 storage with FP64 refinement, told apart by the caller's
+// FP64 or FP32 storage with the FP64 solve, told apart by the caller's
 // loads and stores alone: the serving kernel, which meets both.
 constexpr int kFormBoth = 3;
 
@@ -653,11 +656,10 @@ __device__ __forceinline__ float bg_step32(const Arrow1f& P, float x, bool& stop
 
 // ---------------------------------------------------------------------------
 // The whole solve.  Input: the 6 unique entries (any doubles).  Output: lam
-// ascending, V[3r + c] = row r of eigenvector c.  kFormF32R takes an FP32
-// estimate of each zero, one FP64 Newton step and an FP64
-// re-orthogonalisation; kFormF32 uses the zeros of an FP32 Borges-Gragg
-// iteration as they are, with the paper's vector formulas (zeros the FP32
-// finder cannot give still go to FP64 BG).
+// ascending, V[3r + c] = row r of eigenvector c.  kFormF32R differs from
+// kFormF64 in its storage, its count of evaluations and the flags it knows;
+// kFormF32 uses the zeros of an FP32 Borges-Gragg iteration as they are
+// (zeros that it cannot give still come from the FP64 finder).
 // Returns branch | it_mu << 8 | it_nu << 16.  bad is set for a matrix with
 // a NaN or infinite entry: its outputs are then meaningless (the solve runs
 // on the non-finite values, every loop bounded) and the caller stores NaN in

@@ -60,3 +60,17 @@ def test_planes_half_a_gigabyte_apart():
         assert torch.equal(l, lam) and torch.equal(v, V), ld
         del l, v
         torch.cuda.empty_cache()
+
+
+def test_eigenvalues_alone_from_planes_half_a_gigabyte_apart():
+    """The same for the input's planes, whose stride chooses the order where
+    only eigenvalues are asked for."""
+    n = 4100 * BLOCK + 33
+    A, _ = gen.stress_mix(n, 62, "cuda")
+    lam, _ = _pieces(A)
+    for ld in (1 << 26, (1 << 26) - (1 << 13), (1 << 26) + (1 << 14)):
+        B = _strided(6, n, ld, 0, A.dtype)
+        B.copy_(A)
+        assert torch.equal(s3.syev3(B, vectors=False)[0], lam), ld
+        del B
+        torch.cuda.empty_cache()
