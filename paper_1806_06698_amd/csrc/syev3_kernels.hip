@@ -337,13 +337,20 @@ constexpr int64_t kManyBlocks = 3072;
 //    for AoS chunks of 32 (2^24: 390 against 399; 60 M: 1406 against 1475)
 //    and, where the plane stride comes within 64 KB of a multiple of 2^29
 //    bytes, so that all planes meet the same channels at once, chunks of
-//    256 (2^26 + 4096: 1677 against 1837; 2^27: 3424 against 3543; 2^26:
-//    1626 against 1751 on one device, 1674 against 1670 on another).  FP64
-//    eigenvalues alone do the same (2^26: 761 against 820; 2^26 + 4096: 773
-//    against 825; 2^27: 1517 against 1695; 2^25, 268 MB: 410 against 370),
-//    and the unrefined FP32 form at 2^28 bytes (2^26: 908 against 961); the
-//    refined one gains nothing from it (912 against 918; 1014 against 954 on
-//    another device; eigenvalues alone 2^27: 1081 against 1080).
+//    256.  How bad that is depends on where the pages of an allocation lie:
+//    2^26, 16 allocations on two devices, mean 1690, worst 1870 (with 2
+//    workgroups per compute unit 1705 and 1883, with 4 1710 and 1863); N(0,1)
+//    1733 and 1851, without the cap 1800 and 1904, in launch order 1848 and
+//    2003.  2^26 + 4096: 1696 against 1796 in launch order; 2^27: 3493
+//    against 3718.  Where the multiple is one of 2^31 chunks of 32 do better:
+//    2^28 mean of four allocations 6030, in chunks of 256 6703, in launch
+//    order 6291 (at 2^27 3481, no clear gain).
+//    FP64 eigenvalues alone take the chunks of 256 (2^26: 761 against 820;
+//    2^26 + 4096: 773 against 825; 2^27: 1517 against 1695; but 2^25, 2^28
+//    bytes: 410 against 370), and the unrefined FP32 form does at 2^28 bytes
+//    (2^26: 908 against 961); the refined one gains nothing from them (912
+//    against 918; 1014 against 954 on another device; eigenvalues alone 2^27:
+//    1081 against 1080).
 template <int FORM, bool VECS>
 static Motion motion(int64_t blocks, const void* A, Strides ld, int layout, const void* lambda,
                      const void* V, uint32_t flags) {
@@ -358,9 +365,12 @@ static Motion motion(int64_t blocks, const void* A, Strides ld, int layout, cons
                                               valu ? 0 : kLdsFor3 - kAosLds<T>};
     return Motion{launch, true, 0};
   }
-  const uint64_t far = FORM == kFormF64 ? 1u << 29 : 1u << 28;
-  const uint64_t off = ((uint64_t)(VECS ? ld.v : ld.a) * sizeof(T) + (1u << 16)) & (far - 1);
-  const bool aliased = FORM != kFormF32R && off <= (1u << 17);
+  // the planes' distance is within 64 KB of a multiple of 2^log2 bytes
+  const auto near = [&](int log2) {
+    const uint64_t stride = (uint64_t)(VECS ? ld.v : ld.a) * sizeof(T);
+    return ((stride + (1u << 16)) & (((uint64_t)1 << log2) - 1)) <= (1u << 17);
+  };
+  const bool aliased = FORM != kFormF32R && near(FORM == kFormF64 ? 29 : 28);
   if (!VECS)
     return Motion{FORM == kFormF64 && aliased ? chunked_order(blocks, 8) : launch, true, 0};
   const uintptr_t bits = (uintptr_t)A | (uintptr_t)lambda | (uintptr_t)V |
@@ -369,7 +379,8 @@ static Motion motion(int64_t blocks, const void* A, Strides ld, int layout, cons
   if (kHbmBound ? ragged || !many : ragged && many)
     return Motion{blocks >= 1280 ? chunked_order(blocks, 5) : launch, false,
                   kHbmBound && many && !valu ? kLdsFor3 : 0};
-  return Motion{aliased ? chunked_order(blocks, 8) : launch, true,
+  const uint32_t chunk = kHbmBound && near(31) ? 5 : 8;
+  return Motion{aliased ? chunked_order(blocks, chunk) : launch, true,
                 kHbmBound && !valu ? kLdsFor3 : 0};
 }
 

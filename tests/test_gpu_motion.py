@@ -51,11 +51,12 @@ def test_limits(n, dtype):
 
 def test_planes_half_a_gigabyte_apart():
     """Plane strides at and within 64 KB of 2^29 bytes (chunks of 256 tiles),
-    and just outside."""
+    just outside, and at 2^31 bytes (chunks of 32)."""
     n = 4100 * BLOCK + 33
     A, _ = gen.stress_mix(n, 61, "cuda")
     lam, V = _pieces(A)
-    for ld in (1 << 26, (1 << 26) - (1 << 13), (1 << 26) + (1 << 13), (1 << 26) + (1 << 14)):
+    for ld in (1 << 26, (1 << 26) - (1 << 13), (1 << 26) + (1 << 13), (1 << 26) + (1 << 14),
+               1 << 28):
         l, v = s3.syev3(A, out=(_strided(3, n, ld, 0, A.dtype), _strided(9, n, ld, 0, A.dtype)))
         assert torch.equal(l, lam) and torch.equal(v, V), ld
         del l, v
