@@ -166,10 +166,10 @@ int batched_syev3_ex(int64_t n, const void* A, int64_t ld, int layout,
  * without copies.  Performance note: the 18 planes are streamed together,
  * each wavefront touching all of them at the same element offset, so how
  * fast a very large batch runs depends on which HBM channels the planes'
- * physical pages share.  On an MI355X a 2^28-matrix FP64 solve took 6.2 to
- * 8.3 ms from one allocation to the next (the AoS layout, three streams,
- * 6.4 to 6.9 ms); within one allocation, strides 32.5 KiB longer than n
- * were as fast or up to 7% slower.
+ * physical pages share.  On an MI355X a 2^28-matrix FP64 solve took 5.9 to
+ * 7.0 ms from one allocation to the next (the AoS layout, three streams, 6.4
+ * ms).  Planes that all start on a 128-byte line are the fastest (60 M
+ * matrices 1458 us, off it 1592).
  * Arrays whose plane ranges interleave are refused (SYEV3_E_ALIAS) even
  * when their planes do not overlap.  Errors as batched_syev3_ex.
  */
@@ -308,8 +308,8 @@ typedef struct {
 
 /* Defaults: 64 GiB pool, 4096 slots, 4 ticks in flight, 256 segments/tick,
  * one workgroup per tile, graphs on (launched directly instead, the table
- * copy and the kernel complete 15-20 us sooner at low load, with the same
- * throughput at saturation). */
+ * copy and the kernel complete 12-20 us sooner at low load and serve 6-20%
+ * more at saturation). */
 void syev3_server_default_opts(syev3_server_opts* opts);
 
 /* Create a server on the current device.  Allocates the pool and starts the

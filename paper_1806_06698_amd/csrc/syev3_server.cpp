@@ -401,15 +401,14 @@ int syev3_server::init(const syev3_server_opts& opts) {
   // By default one workgroup per tile of each tick.  A workgroup that goes
   // on to a second tile likely waits, before that tile's loads complete, for
   // the first tile's stores as well (one counter tracks both), which one that
-  // ends after its stores never does: on a tick of 202 stress-mix requests
-  // (16.8 M matrices) the kernel took 0.49 ms with one workgroup per tile
-  // against 0.59 ms with 32 per compute unit striding over the tiles, and
-  // the serving load (input views, 256 requests in flight) served 35.9 G
-  // matrices/s with a fixed 32768 workgroups against 33.0 with 8192 (32
-  // per compute unit).  A fixed grid
-  // far above the tiles costs latency instead (workgroups with no tile:
-  // p50 at 2000 requests/s 0.07 ms with 131072, 0.15 ms with 524288), so
-  // the grid is sized per tick.
+  // ends after its stores never does: an earlier kernel took 0.49 ms for a
+  // tick of 202 stress-mix requests (16.8 M matrices) against 0.59 ms with 32
+  // workgroups per compute unit striding over the tiles.  The serving load
+  // (input views, 256 requests in flight) serves 36.1 to 40.2 G matrices/s
+  // now, 34.2 to 36.6 with at most 8192 workgroups (32 per compute unit).  A
+  // fixed grid far above the tiles costs latency instead (workgroups with no
+  // tile: p50 at 2000 requests/s 0.07 ms with 131072, 0.15 ms with 524288),
+  // so the grid is sized per tick.
   grid_cap = o.grid_blocks > 0 ? o.grid_blocks : (int64_t)1 << 24;
   ticks.resize(o.max_inflight_ticks);
   for (auto& tk : ticks) {
@@ -526,8 +525,8 @@ void syev3_server_default_opts(syev3_server_opts* o) {
   o->max_segments_per_tick = 256;
   o->grid_blocks = 0;
   // ticks replay a graph captured once per slot (direct launches, the
-  // option, complete 15-20 us sooner at low load, with the same throughput
-  // at saturation)
+  // option, complete 12-20 us sooner at low load and serve 6-20% more at
+  // saturation)
   o->use_graphs = 1;
 }
 
