@@ -414,10 +414,12 @@ int syev3_server_get_stats(syev3_server* s, syev3_server_stats* out);
  * may be reused as soon as the call returns.  The solve is enqueued on
  * `stream`.
  *
- * Calls of at most 56 segments share nothing and may overlap.  Every larger
- * call on one GPU uses that GPU's one table, which keeps the last such
- * call's contents (each call writes all of the table it reads).  Larger calls
- * in one stream's order are safe; ones that overlap on one GPU (on streams
+ * Calls of at most 56 segments share nothing and may overlap, and a captured
+ * one replays with its own table.  (A captured larger call copies the
+ * library's host image of the table again at each replay: the last larger
+ * call's.)  Every larger call on one GPU uses that GPU's one table, which keeps
+ * the last such call's contents (each call writes all of the table it reads).
+ * Larger calls in one stream's order are safe; ones that overlap on one GPU (on streams
  * not ordered with each other) race, and a kernel may then read a table
  * that another call has overwritten.  The table's device address
  * is looked up at the first call on each GPU and kept: after a

@@ -64,3 +64,32 @@ def test_calls_on_two_streams():
         for i, (_, l, v) in enumerate(segs):
             c = (20 * k + i) * 1000
             assert torch.equal(l, lam[:, c:c + 1000]) and torch.equal(v, V[:, c:c + 1000])
+
+
+def test_a_captured_call_replays_with_its_own_table():
+    """56 requests captured in a graph; before each replay new inputs, the
+    outputs cleared and a call on other requests."""
+    A, _ = gen.stress_mix(56 * 300, 82, "cuda")
+
+    def requests(k, n):
+        return [(A[:, i * n:(i + 1) * n], torch.zeros(3, n, dtype=A.dtype, device="cuda"),
+                 torch.zeros(9, n, dtype=A.dtype, device="cuda")) for i in range(k)]
+
+    segs, other = requests(56, 300), requests(60, 10)
+    s3.syev3_solve_segments_noalloc(segs)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        s3.syev3_solve_segments_noalloc(segs)
+    for rep in range(4):
+        A.copy_(gen.stress_mix(56 * 300, 83 + rep, "cuda")[0])
+        lam, V = s3.syev3(A)
+        for _, l, v in segs:
+            l.zero_()
+            v.zero_()
+        s3.syev3_solve_segments_noalloc(other)
+        graph.replay()
+        torch.cuda.synchronize()
+        for i, (_, l, v) in enumerate(segs):
+            assert torch.equal(l, lam[:, i * 300:(i + 1) * 300]), (rep, i)
+            assert torch.equal(v, V[:, i * 300:(i + 1) * 300]), (rep, i)
