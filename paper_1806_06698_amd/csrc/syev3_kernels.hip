@@ -324,10 +324,11 @@ constexpr int64_t kManyBlocks = 3072;
 //    to memory, so loads and stores go through L2 as usual, and chunks of 32
 //    tiles keep neighbours on one XCD's L2: FP64 16,777,293 matrices 435
 //    against 607 with the hints in launch order (487 without either), 60 M
-//    1592 against 2154; FP32 30 M 430 against 585.  Three planes of
-//    eigenvalues alone lose little to it and keep the hints (FP64 30 M 380
-//    against 384), as does FP32 storage below kManyBlocks (500,003: 9.6
-//    against 10.2).
+//    1592 against 2154; FP32 30 M 404 against 585.  FP32 storage does so
+//    from 2048 blocks (whole calls: 700,001 11.3 against 14.9, 570,001 10.4
+//    against 11.2, 500,003 9.3 either way, 300,489 8.2 against 7.5); three
+//    planes of eigenvalues alone lose little to it and keep the hints (FP64
+//    30 M 380 against 384).
 //  * FP64 vectors below kManyBlocks take the plain accesses for any planes:
 //    inputs and results of such a batch stay in the caches (400,000: 10.4
 //    against 14.8).  The chunked order pays from 1280 blocks (400,000: 10.4
@@ -376,7 +377,7 @@ static Motion motion(int64_t blocks, const void* A, Strides ld, int layout, cons
   const uintptr_t bits = (uintptr_t)A | (uintptr_t)lambda | (uintptr_t)V |
                          (uintptr_t)(ld.a | ld.l | ld.v) * sizeof(T);
   const bool ragged = (bits & 127u) != 0;
-  if (kHbmBound ? ragged || !many : ragged && many)
+  if (kHbmBound ? ragged || !many : ragged && blocks >= 2048)
     return Motion{blocks >= 1280 ? chunked_order(blocks, 5) : launch, false,
                   kHbmBound && many && !valu ? kLdsFor3 : 0};
   const uint32_t chunk = kHbmBound && near(31) ? 5 : 8;

@@ -75,3 +75,14 @@ def test_eigenvalues_alone_from_planes_half_a_gigabyte_apart():
         assert torch.equal(s3.syev3(B, vectors=False)[0], lam), ld
         del B
         torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("n", [2047 * BLOCK + 1, 2047 * BLOCK - 1])
+def test_unaligned_fp32_planes(n):
+    """Around the size from which FP32 storage with planes off 128-byte lines
+    takes plain accesses and the chunked order."""
+    A, _ = gen.stress_mix(n, 63, "cuda")
+    A = A.float().contiguous()
+    lam, V = _pieces(A)
+    l, v = s3.syev3(A)
+    assert torch.equal(l, lam) and torch.equal(v, V)
