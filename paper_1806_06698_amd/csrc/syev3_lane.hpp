@@ -286,8 +286,8 @@ __device__ __forceinline__ float start_point(const Arrow1& P, const Cubic& Q) {
 //    of F at or below 0, |F'/F| is at most 1/d + 2/x at the distance d from
 //    the sought one, so d is then that small, whatever x > 0 was given; and
 //    the step leaves at most 3 d^3/x^2, that is 2^-51 x, the 2 eps that
-//    bg_update's stop test asks for.  NaN, zero, infinite and (as F' has to
-//    be positive) negative x fail it.
+//    bg_update's stop test asks for.  NaN, zero, infinite (as the comparison
+//    is strict) and, as F' has to be positive, negative x fail it.
 //  * The quotient's error, one v_rcp_f64 and one correction (2^-47), is
 //    relative to a correction of 2^-17 x.
 // 92 cycles per wavefront, against 290 for a Borges-Gragg step with its test.
@@ -301,7 +301,7 @@ __device__ __forceinline__ double halley_step(const Cubic& Q, double x, bool& do
   const double r = __builtin_amdgcn_rcp(den);
   const double d0 = (F * F1) * r;
   const double dx = __builtin_fma(d0, __builtin_fma(-den, r, 1.0), d0);
-  done = dabs(F) <= (0x1.6p-18 * x) * F1 && F1 > 0.0;
+  done = dabs(F) < (0x1.6p-18 * x) * F1 && F1 > 0.0;
   return x - dx;
 }
 
@@ -515,12 +515,21 @@ __device__ __forceinline__ Arrows arrows(double al, double be1, double be2, doub
 
 // Both zeros: their FP32 starts and one Halley step each.  Roots that are
 // not done then take more Halley steps, from the start in FP64 where the
-// first one moved by more than a quarter of x, and those still not done (or
-// all: converge) Borges-Gragg steps to their stop test, from x_inf where
-// Halley's left no positive x.  The two recurrences are independent, so
-// their latencies overlap.  What follows the first steps is a branch of its
-// own, which the empty asm keeps from being evaluated on every lane; it
-// forms the arrows again, so that they need not be held until there.
+// first one moved by more than a quarter of x, and those still not done
+// Borges-Gragg steps from x_inf to their stop test (converge: every root,
+// from the first Halley step's x where that is done).  x_inf lies right of
+// the zero and is formed without cancellation: an arrow whose entries span
+// many orders of magnitude may have a start left of the zero (the chord's
+// constant is then the rounding error of K), from where Halley's steps run
+// to another zero of F, and a Borges-Gragg step back from there, across many
+// orders of magnitude at once, loses its digits.  (Entries of
+// N(0,1) 10^-U(0,40): 92 of 2^20 matrices were wrong without the return to
+// x_inf, by up to infinity; now the worst error of 78 M matrices, with up to
+// 300 for the 40, is 7.4 eps in an emulation on the CPU.)  The two
+// recurrences are independent, so their latencies overlap.  What follows the
+// first steps is a branch of its own, which the empty asm keeps from being
+// evaluated on every lane; it forms the arrows again, so that they need not
+// be held until there.
 __device__ __forceinline__ void zeros_bg(double al, double be1, double be2, double g1,
                                          double g2, double hh, bool converge, double& x1,
                                          double& x2, int& it1, int& it2) {
@@ -533,6 +542,7 @@ __device__ __forceinline__ void zeros_bg(double al, double be1, double be2, doub
   x2 = halley_step(Q2, y2, s2);
   it1 = 1;
   it2 = 1;
+  const bool near1 = s1, near2 = s2;
   if (converge) {
     asm volatile("");
     s1 = s2 = false;
@@ -541,23 +551,29 @@ __device__ __forceinline__ void zeros_bg(double al, double be1, double be2, doub
     asm volatile("" : "+v"(be1), "+v"(be2));
     const Arrows R = arrows(al, be1, be2, g1, g2);
     const Cubic C1 = cubic(R.mu, hh), C2 = cubic(R.nu, hh);
-    if (!s1 && !(dabs(x1 - y1) <= 0.25 * y1)) {
-      asm volatile("");
-      x1 = start_point64(R.mu, C1);
-    }
-    if (!s2 && !(dabs(x2 - y2) <= 0.25 * y2)) {
-      asm volatile("");
-      x2 = start_point64(R.nu, C2);
-    }
     if (!converge) {
+      if (!s1 && !(dabs(x1 - y1) <= 0.25 * y1)) {
+        asm volatile("");
+        x1 = start_point64(R.mu, C1);
+      }
+      if (!s2 && !(dabs(x2 - y2) <= 0.25 * y2)) {
+        asm volatile("");
+        x2 = start_point64(R.nu, C2);
+      }
       for (int t = 0; t < kMaxHalley; ++t) {
         if (s1 && s2) break;
         if (!s1) { ++it1; x1 = halley_step(C1, x1, s1); }
         if (!s2) { ++it2; x2 = halley_step(C2, x2, s2); }
       }
-      const double inf = __builtin_inf();
-      if (!s1 && !(x1 > 0.0 && x1 < inf)) x1 = quad_zero(R.mu.gb, hh, 1.0);
-      if (!s2 && !(x2 > 0.0 && x2 < inf)) x2 = quad_zero(R.nu.gb, hh, 1.0);
+    }
+    // (an x at the end of the range may pass Halley's test and give NaN)
+    if (!(converge ? near1 : s1) || !(x1 > 0.0)) {
+      s1 = false;
+      x1 = quad_zero(R.mu.gb, hh, 1.0);
+    }
+    if (!(converge ? near2 : s2) || !(x2 > 0.0)) {
+      s2 = false;
+      x2 = quad_zero(R.nu.gb, hh, 1.0);
     }
     for (int t = 0; t < kMaxIter; ++t) {
       if (s1 && s2) break;
