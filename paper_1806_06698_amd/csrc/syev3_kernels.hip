@@ -152,25 +152,26 @@ __global__ __launch_bounds__(kBlock) void k_syev3_soa32(uint32_t n, Planes<Stora
 // 16 bytes per lane when the global address is 16-byte aligned (it is for
 // every block when the caller's array is), else one element per lane.
 // total elements; lanes t = 0 .. kBlock - 1.  Measured on 2^26 matrices:
-// 4% faster in FP64 and 9% in FP32 than element-wide copies.
-template <typename T>
+// 4% faster in FP64 and 9% in FP32 than element-wide copies.  NT: the loads'
+// hint (the stores always have it).
+template <bool NT, typename T>
 __device__ __forceinline__ void copy_in(T* sm, const T* g, int total, int t) {
   constexpr int W = 16 / sizeof(T);
   typedef T vec __attribute__((ext_vector_type(W)));
   int k0 = 0;
   if (((uintptr_t)g & 15u) == 0) {
     const int nv = total / W;
-    for (int k = t; k < nv; k += kBlock) ((vec*)sm)[k] = ld<true>((const vec*)g + k);
+    for (int k = t; k < nv; k += kBlock) ((vec*)sm)[k] = ld<NT>((const vec*)g + k);
     k0 = nv * W;
   }
-  for (int k = k0 + t; k < total; k += kBlock) sm[k] = ld<true>(g + k);
+  for (int k = k0 + t; k < total; k += kBlock) sm[k] = ld<NT>(g + k);
 }
 
 // The same for a full tile, whose size is known at compile time: every lane
 // issues all of its loads (or LDS reads) before the first write, so its
 // memory requests are in flight together rather than one after another.
 // g must be 16-byte aligned.  TOTAL = elements, a multiple of 16 / sizeof(T).
-template <typename T, int TOTAL>
+template <bool NT, typename T, int TOTAL>
 __device__ __forceinline__ void copy_in_full(T* sm, const T* g, int t) {
   constexpr int W = 16 / sizeof(T);
   constexpr int NV = TOTAL / W;
@@ -181,7 +182,7 @@ __device__ __forceinline__ void copy_in_full(T* sm, const T* g, int t) {
 #pragma unroll
   for (int j = 0; j < R; ++j) {
     const int k = t + j * kBlock;
-    if (j + 1 < R || k < NV) x[j] = ld<true>((const vec*)g + k);
+    if (j + 1 < R || k < NV) x[j] = ld<NT>((const vec*)g + k);
   }
 #pragma unroll
   for (int j = 0; j < R; ++j) {
@@ -233,7 +234,7 @@ constexpr size_t kAosLds = kBlock * 9 * sizeof(T);
 // rounds, lambda and then V, so the buffer holds 9 values per matrix rather
 // than 12: 18 KB per workgroup in FP64, which lets 8 waves per SIMD fit in
 // the 160 KB of LDS (24 KB allowed only 6).
-template <int FORM, int IN, bool VECS, bool INFO>
+template <int FORM, int IN, bool VECS, bool INFO, bool NT>
 __global__ __launch_bounds__(kBlock) void k_syev3_aos(
     int64_t n, const Storage<FORM>* A, Storage<FORM>* __restrict__ lam, Storage<FORM>* V,
     uint32_t flags, Order order, int32_t* __restrict__ info) {
@@ -247,8 +248,8 @@ __global__ __launch_bounds__(kBlock) void k_syev3_aos(
   // tile but the last, when the caller's arrays are aligned)
   const bool full = cnt == kBlock && ((uintptr_t)A & 15u) == 0 &&
                     ((uintptr_t)lam & 15u) == 0 && (!VECS || ((uintptr_t)V & 15u) == 0);
-  if (full) copy_in_full<T, kBlock * IN>(sm, Ab, t);
-  else copy_in(sm, Ab, cnt * IN, t);
+  if (full) copy_in_full<NT, T, kBlock * IN>(sm, Ab, t);
+  else copy_in<NT>(sm, Ab, cnt * IN, t);
   __syncthreads();
   double a[6];
   if (t < cnt) {
@@ -293,9 +294,9 @@ __global__ __launch_bounds__(kBlock) void k_syev3_aos(
   }
 }
 
-// How a launch moves its data: the workgroup order, the non-temporal hints,
-// and dynamic LDS the kernel does not use, which caps the workgroups a
-// compute unit holds.
+// How a launch moves its data: the workgroup order, the non-temporal hints
+// (in AoS the loads'), and dynamic LDS the kernel does not use, which caps
+// the workgroups a compute unit holds.
 struct Motion {
   Order order;
   bool nt;
@@ -305,6 +306,9 @@ struct Motion {
 // LDS of a workgroup that lets 3 of them (12 wavefronts) onto a compute unit
 // (160 KB) instead of the 8 that the registers allow.
 constexpr size_t kLdsFor3 = 52 << 10;
+constexpr size_t kLdsFor5 = 32 << 10;  // 5 of them
+// An AoS input of at most this much is read with plain loads.
+constexpr int64_t kCachedInput = 64 << 20;
 // From here (786K matrices, 12 workgroups per compute unit) the cap's extra
 // rounds are many enough not to leave compute units idle in the last one.
 constexpr int64_t kManyBlocks = 3072;
@@ -312,12 +316,26 @@ constexpr int64_t kManyBlocks = 3072;
 // The rules, each with both sides measured (us; three sets of buffers in
 // turn, N(0,1) matrices):
 //  * FP64 with vectors, bound by HBM, caps its workgroups at 3 per compute
-//    unit from kManyBlocks on: fewer wavefronts mix fewer reads into the
-//    writes, and 12 per compute unit still cover the solve.  SoA 2^24 393
-//    (cap) against 426, 60 M 1458 against 1602; AoS 2^24 390 against 445.
-//    Below, the cap costs whole rounds (400,000: 13.2 against 10.4).
-//    Eigenvalues only and FP32 storage (72 bytes or less per matrix) need
-//    the wavefronts: FP32 vectors 2^24 212 without the cap, 286 with it.
+//    unit (SoA from kManyBlocks on, AoS from 16384 blocks): fewer wavefronts
+//    mix fewer reads into the writes, and 12 per compute unit still cover the
+//    solve.  SoA 2^24 393 (cap) against 426, 60 M 1458 against 1602; AoS 2^24
+//    390 against 445, full matrices 440 against 520.  Below, the cap costs
+//    whole rounds (400,000: 13.2 against 10.4).  Eigenvalues only and FP32
+//    storage (72 bytes or less per matrix) need the wavefronts: FP32 vectors
+//    2^24 212 without the cap, 286 with it.
+//  * AoS FP64 with vectors caps them at 5 from 2560 to 16384 blocks: the
+//    stress mix, slower to solve, needs more than 3 (2 M packed matrices 49.5
+//    against 52.0; N(0,1) 48.8 either way).  And where its input may be found
+//    in the memory-side cache (up to 64 MB: 1.4 M packed matrices, 932 K full
+//    ones) it is loaded without the hint.  Mean of N(0,1), stress-mix and SPD
+//    matrices over 1 and 4 sets of buffers in turn, against the hint in
+//    launch order (from kManyBlocks on with the cap of 3): packed 400,000 9.0
+//    against 10.0, 500,000 11.3 against 13.0, 640,000 14.9 against 20.3, 2^20
+//    23.6 against 26.7; full 400,000 10.0 against 14.8, 640,000 18.2 against
+//    22.7, 900,000 24.5 against 26.5.  The plain loads without the cap: 2^20
+//    packed 27.8; with it below 2560 blocks: full 400,000 11.2.  Beyond 64 MB
+//    buffers that are not in the cache lose by plain loads (full 2 M
+//    matrices, 4 sets: 58.7 against 55.9).
 //  * SoA planes that do not all start on a 128-byte line (any odd n, for
 //    one): neighbouring wavefronts, and at a tile's edge neighbouring
 //    workgroups, share lines.  Non-temporal stores then write partial lines
@@ -335,8 +353,8 @@ constexpr int64_t kManyBlocks = 3072;
 //    against 11.5; 300,001: 9.0 against 8.7).
 //  * Otherwise the hints: FP64 vectors 2^24 393 against 406 without.  The
 //    order is launch order (60 M: 1458, in chunks of 256 tiles 1569), but
-//    for AoS chunks of 32 (2^24: 390 against 399; 60 M: 1406 against 1475)
-//    and, where the plane stride comes within 64 KB of a multiple of 2^29
+//    for AoS FP64 vectors chunks of 32 (2^24: 390 against 399; 60 M: 1406
+//    against 1475) and, where the plane stride comes within 64 KB of a multiple of 2^29
 //    bytes, so that all planes meet the same channels at once, chunks of
 //    256.  How bad that is depends on where the pages of an allocation lie:
 //    2^26, 16 allocations on two devices, mean 1690, worst 1870 (with 2
@@ -362,9 +380,11 @@ static Motion motion(int64_t blocks, const void* A, Strides ld, int layout, cons
   const bool valu = flags & (kFlagNewton | kFlagPaperBG);
   const bool many = blocks >= kManyBlocks;
   if (layout != 0) {
-    if (kHbmBound && many) return Motion{chunked_order(blocks, 5), true,
-                                              valu ? 0 : kLdsFor3 - kAosLds<T>};
-    return Motion{launch, true, 0};
+    if (!kHbmBound) return Motion{launch, true, 0};
+    const int64_t in_bytes = blocks * kBlock * (layout == 1 ? 6 : 9) * (int64_t)sizeof(T);
+    const bool cached = in_bytes <= kCachedInput;
+    const size_t lds = blocks >= 16384 ? kLdsFor3 : blocks >= 2560 ? kLdsFor5 : kAosLds<T>;
+    return Motion{chunked_order(blocks, 5), !cached, valu ? 0 : lds - kAosLds<T>};
   }
   // the planes' distance is within 64 KB of a multiple of 2^log2 bytes
   const auto near = [&](int log2) {
@@ -418,12 +438,21 @@ static hipError_t launch_t(int64_t n, const void* A, Strides ld, int layout,
     else
       launch_soa<FORM, VECS, INFO, !VECS>(n, A, ld, lambda, V, flags, m, info, grid, block,
                                           stream);
-  } else if (layout == 1) {
-    hipLaunchKernelGGL((k_syev3_aos<FORM, 6, VECS, INFO>), grid, block, m.lds, stream, n,
-                       (const T*)A, (T*)lambda, (T*)V, flags, m.order, info);
   } else {
-    hipLaunchKernelGGL((k_syev3_aos<FORM, 9, VECS, INFO>), grid, block, m.lds, stream, n,
-                       (const T*)A, (T*)lambda, (T*)V, flags, m.order, info);
+    // FP64 with vectors alone has plain loads
+    constexpr bool kPlain = FORM == kFormF64 && VECS;
+    const auto launch = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, grid, block, m.lds, stream, n, (const T*)A, (T*)lambda, (T*)V,
+                         flags, m.order, info);
+    };
+    const bool nt = m.nt || !kPlain;
+    if (layout == 1) {
+      if (nt) launch(k_syev3_aos<FORM, 6, VECS, INFO, true>);
+      else launch(k_syev3_aos<FORM, 6, VECS, INFO, !kPlain>);
+    } else {
+      if (nt) launch(k_syev3_aos<FORM, 9, VECS, INFO, true>);
+      else launch(k_syev3_aos<FORM, 9, VECS, INFO, !kPlain>);
+    }
   }
   return hipGetLastError();
 }

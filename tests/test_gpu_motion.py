@@ -86,3 +86,24 @@ def test_unaligned_fp32_planes(n):
     lam, V = _pieces(A)
     l, v = s3.syev3(A)
     assert torch.equal(l, lam) and torch.equal(v, V)
+
+
+@pytest.mark.parametrize("blocks", [2559, 2560, 3640, 3641, 5461, 5462, 16383, 16384])
+def test_packed_rows(blocks):
+    """AoS FP64 around the limits of its workgroup caps (2560 and 16384 blocks)
+    and of the plain loads (64 MB of input: 5461 blocks of packed rows, 3640 of full
+    matrices), with a full and a short last tile; full matrices also solved
+    in place, also from an address that no 16-byte load may take."""
+    for n in (blocks * BLOCK, blocks * BLOCK - 100):
+        A, _ = gen.stress_mix(n, 64, "cuda")
+        lam, V = _pieces(A)
+        full = gen.to_full(A).contiguous()
+        for layout, rows in (("aos", gen.to_aos(A).contiguous()), ("aos9", full),
+                             ("aos9", full.reshape(n, 9))):
+            l, v = s3.syev3(rows, layout=layout)
+            assert torch.equal(l.t(), lam) and torch.equal(v.reshape(n, 9).t(), V), layout
+        for first in (0, 1):
+            M = torch.empty(9 * n + first, dtype=A.dtype,
+                            device="cuda")[first:].view(n, 3, 3).copy_(full)
+            l = s3.syev3_inplace(M)
+            assert torch.equal(l.t(), lam) and torch.equal(M.reshape(n, 9).t(), V), first
