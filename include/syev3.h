@@ -398,8 +398,8 @@ int syev3_server_get_stats(syev3_server* s, syev3_server_stats* out);
  * the kernel that runs a server's ticks, on buffers the caller owns.  That
  * kernel reads a table of the requests; a server allocates one per tick
  * slot in syev3_server_create.  Here it is the launch's kernel argument for
- * at most 56 segments with n > 0; for more, this call uses a fixed array of
- * the library in each GPU's memory (room for SYEV3_SEGMENTS_MAX segments,
+ * at most 56 segments with n > 0 and under capture; else this call uses a
+ * fixed array of the library in each GPU's memory (room for SYEV3_SEGMENTS_MAX segments,
  * about 72 KiB, held until the process ends).  It makes no hipMalloc,
  * hipFree or other allocating call.  Results are bitwise those of the same requests
  * served by a server or solved by batched_syev3_strided.
@@ -414,15 +414,15 @@ int syev3_server_get_stats(syev3_server* s, syev3_server_stats* out);
  * may be reused as soon as the call returns.  The solve is enqueued on
  * `stream`.
  *
- * Calls of at most 56 segments share nothing and may overlap, and a captured
- * one replays with its own table.  (A captured larger call copies the
- * library's host image of the table again at each replay: the last larger
- * call's.)  Every larger call on one GPU uses that GPU's one table, which keeps
- * the last such call's contents (each call writes all of the table it reads).
- * Larger calls in one stream's order are safe; ones that overlap on one GPU (on streams
- * not ordered with each other) race, and a kernel may then read a table
- * that another call has overwritten.  The table's device address
- * is looked up at the first call on each GPU and kept: after a
+ * Calls of at most 56 segments and calls under capture (of any size: 56
+ * segments a launch) share nothing and may overlap, and a captured call
+ * replays with its own table.  Every larger call on one GPU uses that GPU's
+ * one table, which keeps the last such call's contents (each call writes all
+ * of the table it reads).
+ * Larger calls in one stream's order are safe; ones that overlap on one GPU
+ * (on streams not ordered with each other) race, and a kernel may then read a
+ * table that another call has overwritten.  The table's device address is
+ * looked up at the first call on each GPU and kept: after a
  * hipDeviceReset of that GPU the call must not be used again in the
  * process.
  *

@@ -74,9 +74,10 @@ def syev3_solve_segments_noalloc(segments, *, stream=None) -> None:
     V, flags) per request, all on one GPU: A (6, n) float64 (FP64) or float32
     (FP32 storage + FP64 refinement) with unit column stride and row stride
     >= n; lam (3, n) and V (9, n) or None, contiguous, of A's dtype; they are
-    written in place.  Asynchronous on the stream; calls on one GPU that are
-    not ordered on one stream race (they share the library's segment
-    table)."""
+    written in place.  Asynchronous on the stream.  Calls of more than 56
+    requests on one GPU that are not ordered on one stream race (they share
+    the library's segment table); smaller calls and calls under graph capture
+    share nothing."""
     # the valid call on plain tensors, natively (3 us per request here)
     native = _lib.binding().segments
     if native(segments, None, None) if stream is None else \

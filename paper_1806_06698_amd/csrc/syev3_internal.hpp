@@ -101,9 +101,10 @@ hipError_t launch_segments_host(const HostTable& table, hipStream_t stream);
 
 // launch_segments for host_table (nseg segments, total_tiles > 0; its cap and what
 // follows the segments are not read) with no allocation: as the kernel's
-// argument up to kInlineSegments segments, else copied into the library's
-// fixed table of the stream's device.  That copy is from pageable host
-// memory, which HIP completes before returning.
+// argument up to kInlineSegments segments (and under capture, in as many
+// launches as it takes), else copied into the library's fixed table of the
+// stream's device.  That copy is from pageable host memory, which HIP
+// completes before returning.
 hipError_t launch_segments_noalloc(const TickTable* host_table, hipStream_t stream);
 
 }  // namespace syev3

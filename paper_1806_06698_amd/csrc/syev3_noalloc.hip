@@ -35,6 +35,9 @@ void* g_scratch[kMaxDevices] = {};
 std::mutex g_image_mu;
 alignas(16) unsigned char g_image[kTableBytes];
 
+// One workgroup per tile (as a server's ticks), up to 2^24.
+int32_t grid_of(int64_t tiles) { return (int32_t)std::min<int64_t>(tiles, (int64_t)1 << 24); }
+
 hipError_t scratch_of_device(int dev, TickTable** out) {
   if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
   std::lock_guard<std::mutex> lock(g_scratch_mu);
@@ -58,24 +61,42 @@ hipError_t scratch_of_device(int dev, TickTable** out) {
 
 }  // namespace
 
+// Segments first .. first + count - 1 of the table in one launch whose kernel
+// argument they are, their tiles counted from the first one's.
+static hipError_t launch_part(const TickTable* host_table, int first, int count,
+                              hipStream_t stream) {
+  const Segment* seg = host_table->seg + first;
+  const int64_t end = first + count < host_table->nseg ? seg[count].tile_begin
+                                                       : host_table->total_tiles;
+  InlineTable t;
+  t.nseg = count;
+  t.cap = kInlineSegments;
+  t.total_tiles = end - seg[0].tile_begin;
+  for (int i = 0; i < count; ++i) {
+    t.seg[i] = seg[i];
+    t.begin[i] = t.seg[i].tile_begin -= seg[0].tile_begin;
+  }
+  (void)hipGetLastError();  // launch_segments_inline reads it: drop any stale error
+  return launch_segments_inline(t, grid_of(t.total_tiles), stream);
+}
+
 hipError_t launch_segments_noalloc(const TickTable* host_table, hipStream_t stream) {
   const int nseg = host_table->nseg;
-  // one workgroup per tile (as a server's ticks), up to 2^24
-  const int32_t grid = (int32_t)std::min<int64_t>(host_table->total_tiles, (int64_t)1 << 24);
-  if (nseg <= kInlineSegments) {
-    InlineTable t;
-    t.nseg = nseg;
-    t.cap = kInlineSegments;
-    t.total_tiles = host_table->total_tiles;
-    for (int i = 0; i < nseg; ++i) {
-      t.begin[i] = host_table->seg[i].tile_begin;
-      t.seg[i] = host_table->seg[i];
+  hipError_t e;
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  // (the default stream cannot be captured)
+  if (nseg > kInlineSegments && stream &&
+      (e = hipStreamIsCapturing(stream, &capture)) != hipSuccess)
+    return e;
+  if (nseg <= kInlineSegments || capture != hipStreamCaptureStatusNone) {
+    for (int i = 0; i < nseg; i += kInlineSegments) {
+      e = launch_part(host_table, i, std::min(nseg - i, kInlineSegments), stream);
+      if (e != hipSuccess) return e;
     }
-    (void)hipGetLastError();  // launch_segments_inline reads it: drop any stale error
-    return launch_segments_inline(t, grid, stream);
+    return hipSuccess;
   }
   int dev = 0;
-  hipError_t e = stream ? hipStreamGetDevice(stream, &dev) : hipGetDevice(&dev);
+  e = stream ? hipStreamGetDevice(stream, &dev) : hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   TickTable* table = nullptr;
   if ((e = scratch_of_device(dev, &table)) != hipSuccess) return e;
@@ -91,7 +112,7 @@ hipError_t launch_segments_noalloc(const TickTable* host_table, hipStream_t stre
   e = hipMemcpyAsync(table, image, tick_table_bytes(nseg), hipMemcpyHostToDevice, stream);
   if (e != hipSuccess) return e;
   (void)hipGetLastError();  // launch_segments reads it: drop any stale error
-  return launch_segments(table, grid, stream);
+  return launch_segments(table, grid_of(image->total_tiles), stream);
 }
 
 }  // namespace syev3
