@@ -6,7 +6,9 @@ kernels.  Loading fails loudly if the library has not been built.
 from __future__ import annotations
 
 import ctypes
+import importlib
 import os
+import warnings
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "libsyev3.so")
@@ -136,17 +138,40 @@ def lib() -> ctypes.CDLL:
     return L
 
 
+class _PythonOnly:
+    """In place of the native binding: every call takes the Python code."""
+
+    @staticmethod
+    def solve(*args):
+        return None
+
+    @staticmethod
+    def segments(*args):
+        return None
+
+
 def binding():
-    """The native fast paths of this package's calls (csrc/syev3_binding.cpp;
-    raises if it is not built)."""
+    """The native fast paths of this package's calls (csrc/syev3_binding.cpp).
+    They are compiled against one build of torch: where they are missing, do
+    not load or were built for another torch, a warning says so once and every
+    call takes the Python code, which makes the same C calls."""
     global _binding
     if _binding is None:
-        lib()
-        if not os.path.exists(BINDING_PATH):
-            raise RuntimeError(
-                f"{BINDING_PATH} is missing: build it with `python -m paper_1806_06698_amd.build`")
-        from . import _binding as module
-        _binding = module
+        import torch
+        try:
+            lib()  # before the module, which is linked to it
+            module = importlib.import_module("._binding", __package__)
+            if module.torch_version != torch.__version__:
+                raise ImportError(f"it was built for torch {module.torch_version}, "
+                                  f"this is {torch.__version__}")
+            _binding = module
+        except (ImportError, OSError, RuntimeError) as e:
+            if not os.path.exists(LIB_PATH):
+                return _PythonOnly  # the Python code reports it
+            _binding = _PythonOnly
+            warnings.warn(f"calls take the slower Python code: {BINDING_PATH} is not usable "
+                          f"({e}); rebuild with `python -m paper_1806_06698_amd.build`",
+                          RuntimeWarning, stacklevel=3)
     return _binding
 
 

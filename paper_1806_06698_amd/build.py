@@ -81,8 +81,34 @@ def build(verbose: bool = False) -> str:
     return LIB
 
 
-def build_binding(cc: str, verbose: bool = False) -> str:
-    """Compile the binding (host code only) against the library just built."""
+def binding_needs() -> str:
+    """What this machine lacks to compile the binding ("" if nothing)."""
+    if not (shutil.which("g++") or shutil.which("c++")):
+        return "a host C++ compiler"
+    if not os.path.exists(os.path.join(sysconfig.get_paths()["include"], "Python.h")):
+        return "Python's headers"
+    try:
+        import torch
+        from torch.utils import cpp_extension
+    except ImportError:
+        return "torch"
+    if not any(os.path.exists(os.path.join(d, "torch", "csrc", "autograd", "python_variable.h"))
+               for d in cpp_extension.include_paths()):
+        return "torch's headers"
+    return ""
+
+
+def build_binding(cc: str, verbose: bool = False) -> str | None:
+    """Compile the binding (host code only) against the library just built.
+    The library and the package work without it: where this machine cannot
+    compile it, says so and returns None."""
+    if os.path.exists(BINDING):
+        os.remove(BINDING)  # never a binding of other sources than the library's
+    needs = binding_needs()
+    if needs:
+        sys.stderr.write(f"{BINDING} is not built (no {needs.removeprefix('a ')} here): calls "
+                         "from Python take the slower Python code\n")
+        return None
     import torch
     from torch.utils import cpp_extension
 
@@ -92,6 +118,7 @@ def build_binding(cc: str, verbose: bool = False) -> str:
     cmd = [shutil.which("g++") or "c++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
            "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           f'-DSYEV3_TORCH_VERSION="{torch.__version__}"',
            "-I", INCLUDE, *[a for d in cpp_extension.include_paths() for a in ("-isystem", d)],
            "-isystem", os.path.join(rocm, "include"),
            "-isystem", sysconfig.get_paths()["include"],
