@@ -80,9 +80,12 @@ def syev3_solve_segments_noalloc(segments, *, stream=None) -> None:
     share nothing."""
     # the valid call on plain tensors, natively (3 us per request here)
     native = _lib.binding().segments
-    if native(segments, None, None) if stream is None else \
-            native(segments, stream.device.index, stream.cuda_stream):
-        return
+    if stream is None:
+        if native(segments, None, None):
+            return
+    elif isinstance(stream, torch.cuda.Stream):
+        if native(segments, stream.device.index, stream.cuda_stream):
+            return
     segs = (_lib.Segment * max(len(segments), 1))()
     device = None
     for i, item in enumerate(segments):

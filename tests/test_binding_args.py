@@ -89,3 +89,13 @@ def test_segment_call_binding_checks_its_tensors():
     lam = torch.empty(3, n, dtype=torch.float64)
     with pytest.raises(ValueError, match="GPU"):
         s3.syev3_solve_segments_noalloc([(A, lam, None)])
+
+
+def test_segment_call_looks_at_its_stream_last():
+    """No segments and host tensors are answered before the stream is looked
+    at, whatever it is."""
+    A = torch.zeros(6, 8, dtype=torch.float64)
+    for stream in (object(), 0, "x"):
+        s3.syev3_solve_segments_noalloc([], stream=stream)
+        with pytest.raises(ValueError, match="GPU"):
+            s3.syev3_solve_segments_noalloc([(A, A[:3], None)], stream=stream)
