@@ -96,40 +96,34 @@ def check_loadgen_sources(src_f64, src_f32, max_log2_n, sink):
 
 
 class Request:
-    """An admitted request: device tensors over the server's pool (A is the
-    caller's own tensor for a request admitted as a view)."""
+    """An admitted request: device tensors A, lam and V (None without vectors)
+    over the server's pool, the request's until its release (A is the caller's
+    own tensor for a request admitted as a view)."""
 
     def __init__(self, server, rid, bufs: RequestBuffers, dtype, A=None):
         self.server, self.id, self.n = server, rid, bufs.n
         self.dtype = bufs.dtype
         self._bufs = bufs
-        # a view's input: the caller's tensor, held until release
-        self._A, self._lam, self._V = A, None, None
+        if A is not None:
+            self.A = A  # a view's input: the caller's tensor, held until release
+        if not bufs.V:
+            self.V = None
         self.host_buffers = None  # held from a host-staged submit to release
 
-    def _tensor(self, ptr, rows):
+    def __getattr__(self, name):
+        # The tensors are made when first asked for, as a host-staged request
+        # needs none, and are ordinary attributes from then on.
+        rows = {"A": 6, "lam": 3, "V": 9}.get(name)
+        if rows is None:
+            raise AttributeError(f"{type(self).__name__!r} object has no attribute {name!r}")
+        if not self.server.h:
+            raise RuntimeError(f"{name}: the server is closed and its memory freed")
         f64 = self.dtype == _lib.F64
-        return _tensor_at(ptr, (rows, self.n), torch.float64 if f64 else torch.float32,
-                          8 if f64 else 4, self.server.device)
-
-    # the tensors are made when asked for: a host-staged request needs none
-    @property
-    def A(self):
-        if self._A is None:
-            self._A = self._tensor(self._bufs.A, 6)
-        return self._A
-
-    @property
-    def lam(self):
-        if self._lam is None:
-            self._lam = self._tensor(self._bufs.lam, 3)
-        return self._lam
-
-    @property
-    def V(self):
-        if self._V is None and self._bufs.V:
-            self._V = self._tensor(self._bufs.V, 9)
-        return self._V
+        t = _tensor_at(getattr(self._bufs, name), (rows, self.n),
+                       torch.float64 if f64 else torch.float32, 8 if f64 else 4,
+                       self.server.device)
+        setattr(self, name, t)
+        return t
 
 
 def _tensor_at(ptr, shape, dtype, esize, dev):
