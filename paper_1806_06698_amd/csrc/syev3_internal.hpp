@@ -97,7 +97,9 @@ struct HostTable {
   int64_t begin[kHostSegments];
   HostSegment seg[kHostSegments];
 };
-hipError_t launch_segments_host(const HostTable& table, hipStream_t stream);
+// At most max_blocks workgroups, which stride over the table's tiles.
+hipError_t launch_segments_host(const HostTable& table, int32_t max_blocks,
+                                hipStream_t stream);
 
 // launch_segments for host_table (nseg segments, total_tiles > 0; its cap and what
 // follows the segments are not read) with no allocation: as the kernel's

@@ -738,8 +738,10 @@ hipError_t launch_segments_inline(const InlineTable& table, int32_t grid_blocks,
   return hipGetLastError();
 }
 
-hipError_t launch_segments_host(const HostTable& table, hipStream_t stream) {
-  const int64_t grid = std::min<int64_t>(table.total_tiles, kHostBlocks);
+hipError_t launch_segments_host(const HostTable& table, int32_t max_blocks,
+                                hipStream_t stream) {
+  const int64_t grid =
+      std::min<int64_t>(table.total_tiles, std::min<int32_t>(kHostBlocks, max_blocks));
   (void)hipGetLastError();  // read below: drop any stale error
   hipLaunchKernelGGL(k_syev3_segments_host, dim3((unsigned)grid), dim3(kBlock), 0, stream,
                      table);

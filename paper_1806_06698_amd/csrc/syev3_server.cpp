@@ -246,7 +246,7 @@ int syev3_server::launch_tick(int slot) {
       hs.lambda = r.h_lam;
       hs.V = r.h_V;
       if (++ht.nseg == syev3::kHostSegments) {
-        if (e == hipSuccess) e = syev3::launch_segments_host(ht, tk.stream);
+        if (e == hipSuccess) e = syev3::launch_segments_host(ht, (int32_t)grid_cap, tk.stream);
         ht.nseg = 0;
         ht.total_tiles = 0;
       }
@@ -266,7 +266,8 @@ int syev3_server::launch_tick(int slot) {
     }
     if (r.h_lam) staged_out = true;
   }
-  if (ht.nseg > 0 && e == hipSuccess) e = syev3::launch_segments_host(ht, tk.stream);
+  if (ht.nseg > 0 && e == hipSuccess)
+    e = syev3::launch_segments_host(ht, (int32_t)grid_cap, tk.stream);
   t->nseg = nseg;
   t->total_tiles = tiles;
   if (nseg > 0 && e == hipSuccess) {
