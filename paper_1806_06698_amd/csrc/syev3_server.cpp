@@ -196,9 +196,9 @@ bool overlap(const void* a, size_t na, const void* b, size_t nb) {
 // pinned, of aligned values, and no result's memory shared with the input's
 // or another result's (copies finish reading before the results are
 // written, and write the vectors last).
-bool takes_direct(int device, const Request& r, const void* A, void* lam, void* V) {
-  const size_t es = r.dtype == SYEV3_F64 ? 8 : 4;
-  const size_t plane = (size_t)r.n * es, bA = 6 * plane, bl = 3 * plane, bV = V ? 9 * plane : 0;
+bool takes_direct(int device, int64_t n, int dtype, const void* A, void* lam, void* V) {
+  const size_t es = dtype == SYEV3_F64 ? 8 : 4;
+  const size_t plane = (size_t)n * es, bA = 6 * plane, bl = 3 * plane, bV = V ? 9 * plane : 0;
   if (((uintptr_t)A | (uintptr_t)lam | (uintptr_t)V) % es) return false;
   if (overlap(A, bA, lam, bl) || (V && (overlap(A, bA, V, bV) || overlap(lam, bl, V, bV))))
     return false;
@@ -643,12 +643,29 @@ int syev3_server_submit_host(syev3_server* s, int64_t id, const void* host_A,
                              void* host_lambda, void* host_V) {
   if (!s) return SYEV3_E_STATE;
   if (!host_A || !host_lambda) return SYEV3_E_NULL;
+  int64_t n;
+  int dtype;
+  // a view's input is the caller's device memory: there is nothing to stage
+  const auto admitted = [&](int* slot) {
+    Request* r = lookup(s, id, slot);
+    return r && r->state == kAdmitted && !r->view ? r : nullptr;
+  };
+  {
+    std::lock_guard<std::mutex> lk(s->mu);
+    const Request* r = admitted(nullptr);
+    if (!r) return SYEV3_E_STATE;
+    n = r->n;
+    dtype = r->dtype;
+    if (!r->vecs) host_V = nullptr;
+  }
+  // These queries may wait for the runtime's own locks: not under the
+  // server's, which every other client and the scheduler need.
+  const bool direct = takes_direct(s->device, n, dtype, host_A, host_lambda, host_V);
   {
     std::lock_guard<std::mutex> lk(s->mu);
     int slot;
-    Request* r = lookup(s, id, &slot);
-    // a view's input is the caller's device memory: there is nothing to stage
-    if (!r || r->state != kAdmitted || r->view) return SYEV3_E_STATE;
+    Request* r = admitted(&slot);
+    if (!r) return SYEV3_E_STATE;  // submitted or released meanwhile
     try {
       s->queue.push_back(slot);
     } catch (const std::bad_alloc&) {
@@ -658,8 +675,8 @@ int syev3_server_submit_host(syev3_server* s, int64_t id, const void* host_A,
     r->ready = nullptr;
     r->h_A = host_A;
     r->h_lam = host_lambda;
-    r->h_V = r->vecs ? host_V : nullptr;
-    r->direct = takes_direct(s->device, *r, r->h_A, r->h_lam, r->h_V);
+    r->h_V = host_V;
+    r->direct = direct;
     r->t_submit = Clock::now();
     s->note_queue();
     s->st.submitted++;

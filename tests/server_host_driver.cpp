@@ -6,10 +6,12 @@
 // launches are recorded and events have completed at once.
 //
 // Each request must go to the kernel that works on host memory in place
-// exactly when its buffers allow it, and be copied otherwise; and its launch
-// must keep to the server's most workgroups.
+// exactly when its buffers allow it, and be copied otherwise; its launch must
+// keep to the server's most workgroups; and the runtime must not be queried
+// while the server's lock is held.
 #include "syev3_server.cpp"
 
+#include <atomic>
 #include <cstdio>
 #include <cstdlib>
 
@@ -35,6 +37,28 @@ struct Seen {
 } g_seen;
 
 syev3_server* g_server = nullptr;
+std::atomic<int> g_queries{0}, g_under_lock{0};
+
+// Whether another thread gets the server's lock (the scheduler holds it for
+// moments only).
+void query() {
+  ++g_queries;
+  if (!g_server) return;
+  bool got = false;
+  std::thread t([&] {
+    for (int i = 0; i < 100 && !got; ++i) {
+      if (g_server->mu.try_lock()) {
+        g_server->mu.unlock();
+        got = true;
+      } else {
+        std::this_thread::sleep_for(std::chrono::milliseconds(1));
+      }
+    }
+  });
+  t.join();
+  if (!got) ++g_under_lock;
+}
+
 const Alloc* find(uintptr_t p) {
   for (const Alloc& a : g_allocs)
     if (p >= a.base && p < a.base + a.size) return &a;
@@ -114,6 +138,7 @@ hipError_t hipMemcpy2DAsync(void*, size_t, const void*, size_t, size_t, size_t, 
   return hipErrorUnknown;
 }
 hipError_t hipPointerGetAttributes(hipPointerAttribute_t* at, const void* p) {
+  query();
   const Alloc* a = find((uintptr_t)p);
   if (!a) return hipErrorInvalidValue;
   at->type = a->type;
@@ -125,6 +150,7 @@ hipError_t hipPointerGetAttributes(hipPointerAttribute_t* at, const void* p) {
   return hipSuccess;
 }
 hipError_t hipMemGetAddressRange(hipDeviceptr_t* base, size_t* size, hipDeviceptr_t p) {
+  query();
   const Alloc* a = find((uintptr_t)p);
   if (!a) return hipErrorInvalidValue;
   *base = (hipDeviceptr_t)a->base;
@@ -291,6 +317,8 @@ int main() {
     for (int k : g_seen.host_launches) EXPECT(k >= 1 && k <= syev3::kHostSegments, "many");
   }
   EXPECT(g_seen.max_blocks >= 64, "as many workgroups as the kernel wants");
+  EXPECT(g_queries > 0 && g_under_lock == 0, "%d of %d queries under the lock",
+         g_under_lock.load(), g_queries.load());
   syev3_server* s = g_server;
   g_server = nullptr;
   syev3_server_destroy(s);

@@ -1,7 +1,8 @@
 """The server's host-staged requests (syev3_server.cpp) against a model of the
 HIP runtime, host code only, under AddressSanitizer and
-UndefinedBehaviorSanitizer: which buffers the kernel takes in place and how
-many workgroups it may use.  No GPU."""
+UndefinedBehaviorSanitizer: which buffers the kernel takes in place, how many
+workgroups it may use, and that the runtime is not queried under the server's
+lock.  No GPU."""
 import os
 import shutil
 import subprocess
