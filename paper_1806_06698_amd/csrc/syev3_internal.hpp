@@ -101,6 +101,10 @@ struct HostTable {
 hipError_t launch_segments_host(const HostTable& table, int32_t max_blocks,
                                 hipStream_t stream);
 
+// How many of a server's requests that kernel has been launched on: for tests,
+// as its results are those of the copies; not part of the interface.
+extern "C" int64_t syev3_server_solved_in_place(syev3_server* s);
+
 // launch_segments for host_table (nseg segments, total_tiles > 0; its cap and what
 // follows the segments are not read) with no allocation: as the kernel's
 // argument up to kInlineSegments segments (and under capture, in as many

@@ -139,6 +139,7 @@ struct syev3_server {
   std::thread thr;
 
   syev3_server_stats st{};
+  int64_t solved_in_place = 0;
   // completion list for the built-in load generator (off otherwise)
   bool track_done = false;
   std::vector<int64_t> done_ids;
@@ -221,6 +222,12 @@ int syev3_server::launch_tick(int slot) {
   bool staged_out = false;
   hipError_t e = hipSuccess;
   hipEvent_t last_ready = nullptr;
+  const auto launch_host = [&] {
+    if (e == hipSuccess) e = syev3::launch_segments_host(ht, (int32_t)grid_cap, tk.stream);
+    if (e == hipSuccess) solved_in_place += ht.nseg;
+    ht.nseg = 0;
+    ht.total_tiles = 0;
+  };
   tk.reqs.clear();
   while (!queue.empty() && (int)tk.reqs.size() < o.max_segments_per_tick) {
     const int ri = queue.front();
@@ -245,11 +252,7 @@ int syev3_server::launch_tick(int slot) {
       hs.A = r.h_A;
       hs.lambda = r.h_lam;
       hs.V = r.h_V;
-      if (++ht.nseg == syev3::kHostSegments) {
-        if (e == hipSuccess) e = syev3::launch_segments_host(ht, (int32_t)grid_cap, tk.stream);
-        ht.nseg = 0;
-        ht.total_tiles = 0;
-      }
+      if (++ht.nseg == syev3::kHostSegments) launch_host();
       continue;
     }
     ++nseg;
@@ -266,8 +269,7 @@ int syev3_server::launch_tick(int slot) {
     }
     if (r.h_lam) staged_out = true;
   }
-  if (ht.nseg > 0 && e == hipSuccess)
-    e = syev3::launch_segments_host(ht, (int32_t)grid_cap, tk.stream);
+  if (ht.nseg > 0) launch_host();
   t->nseg = nseg;
   t->total_tiles = tiles;
   if (nseg > 0 && e == hipSuccess) {
@@ -746,6 +748,11 @@ int syev3_server_get_stats(syev3_server* s, syev3_server_stats* out) {
   out->queue_depth = (int64_t)s->queue.size();
   if (s->busy_ticks > 0) out->busy_seconds += seconds_since(s->busy_since, Clock::now());
   return SYEV3_OK;
+}
+
+int64_t syev3_server_solved_in_place(syev3_server* s) {
+  std::lock_guard<std::mutex> lk(s->mu);
+  return s->solved_in_place;
 }
 
 int syev3_server_loadgen(syev3_server* s, const syev3_loadgen_opts* o,

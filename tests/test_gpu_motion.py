@@ -107,3 +107,40 @@ def test_packed_rows(blocks):
                             device="cuda")[first:].view(n, 3, 3).copy_(full)
             l = s3.syev3_inplace(M)
             assert torch.equal(l.t(), lam) and torch.equal(M.reshape(n, 9).t(), V), first
+
+
+def test_unrefined_fp32_planes_a_quarter_gigabyte_apart():
+    """The unrefined FP32 form's planes at and next to 2^28 bytes apart."""
+    n = 4100 * BLOCK + 33
+    A, _ = gen.stress_mix(n, 65, "cuda")
+    A = A.float().contiguous()
+    pieces = [s3.syev3(A[:, i:i + PIECE].contiguous(), refine=False)
+              for i in range(0, n, PIECE)]
+    lam, V = (torch.cat(p, 1) for p in zip(*pieces))
+    for ld in (1 << 26, (1 << 26) - (1 << 14), (1 << 26) + (1 << 14), (1 << 26) + (1 << 15)):
+        out = (_strided(3, n, ld, 0, A.dtype), _strided(9, n, ld, 0, A.dtype))
+        l, v = s3.syev3(A, out=out, refine=False)
+        assert torch.equal(l, lam) and torch.equal(v, V), ld
+        del l, v, out
+        torch.cuda.empty_cache()
+
+
+def test_64_bit_offsets_with_aligned_planes():
+    """Planes of more than 2^32 bytes, all on 128-byte lines: the hinted
+    variant of the kernel with 64-bit offsets (an odd count takes the plain
+    one).  The input repeats one piece, and every repeat equals it."""
+    piece = 1 << 20
+    n = (1 << 29) + 64
+    base, _ = gen.stress_mix(piece, 66, "cuda")
+    lam, V = s3.syev3(base)
+    A = torch.empty(6, n, dtype=torch.float64, device="cuda")
+    for i in range(0, n, piece):
+        A[:, i:i + piece] = base[:, :n - i]
+    l, v = s3.syev3(A)
+    del A
+    for i in range(0, n, piece):
+        m = min(piece, n - i)
+        assert torch.equal(l[:, i:i + m], lam[:, :m]), i
+        assert torch.equal(v[:, i:i + m], V[:, :m]), i
+    del l, v
+    torch.cuda.empty_cache()
