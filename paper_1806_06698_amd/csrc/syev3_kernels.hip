@@ -108,9 +108,8 @@ __global__ __launch_bounds__(kBlock) void k_syev3_soa(int64_t n, Planes<Storage<
 
 // The same with a 32-bit byte offset per lane, for n * sizeof(T) < 2^32:
 // loads and stores take the scalar-base addressing form and need no 64-bit
-// address arithmetic per lane.
-
-template <int FORM, bool VECS, bool INFO, bool NT>
+// address arithmetic per lane.  NTL, NTS: the loads' and the stores' hint.
+template <int FORM, bool VECS, bool INFO, bool NTL, bool NTS>
 __global__ __launch_bounds__(kBlock) void k_syev3_soa32(uint32_t n, Planes<Storage<FORM>> P,
                                                        uint32_t flags, Order order,
                                                        int32_t* __restrict__ info) {
@@ -121,7 +120,7 @@ __global__ __launch_bounds__(kBlock) void k_syev3_soa32(uint32_t n, Planes<Stora
   double a[6];
 #pragma unroll
   for (int k = 0; k < 6; ++k)
-    a[k] = (double)ld<NT>((const T*)((const char*)P.a[k] + off));
+    a[k] = (double)ld<NTL>((const T*)((const char*)P.a[k] + off));
   double l[3], v[9];
   bool bad;
   const int code = solve3<VECS, FORM>(a, flags, l, v, bad);
@@ -132,17 +131,17 @@ __global__ __launch_bounds__(kBlock) void k_syev3_soa32(uint32_t n, Planes<Stora
   uint32_t soff = off;
   asm volatile("" : "+v"(soff));
 #pragma unroll
-  for (int j = 0; j < 3; ++j) st<NT>((T)l[j], (T*)((char*)P.l[j] + soff));
+  for (int j = 0; j < 3; ++j) st<NTS>((T)l[j], (T*)((char*)P.l[j] + soff));
   if (VECS) {
 #pragma unroll
-    for (int k = 0; k < 9; ++k) st<NT>((T)v[k], (T*)((char*)P.v[k] + soff));
+    for (int k = 0; k < 9; ++k) st<NTS>((T)v[k], (T*)((char*)P.v[k] + soff));
   }
   if (bad) {  // a NaN or infinite entry: NaN in every output of the matrix
 #pragma unroll
-    for (int j = 0; j < 3; ++j) st<NT>(qnan<T>(), (T*)((char*)P.l[j] + soff));
+    for (int j = 0; j < 3; ++j) st<NTS>(qnan<T>(), (T*)((char*)P.l[j] + soff));
     if (VECS) {
 #pragma unroll
-      for (int k = 0; k < 9; ++k) st<NT>(qnan<T>(), (T*)((char*)P.v[k] + soff));
+      for (int k = 0; k < 9; ++k) st<NTS>(qnan<T>(), (T*)((char*)P.v[k] + soff));
     }
   }
   if (INFO) info[i] = code;
@@ -294,12 +293,12 @@ __global__ __launch_bounds__(kBlock) void k_syev3_aos(
   }
 }
 
-// How a launch moves its data: the workgroup order, the non-temporal hints
-// (in AoS the loads'), and dynamic LDS the kernel does not use, which caps
-// the workgroups a compute unit holds.
+// How a launch moves its data: the workgroup order, the loads' and the stores'
+// non-temporal hints (AoS stores always have theirs), and dynamic LDS the
+// kernel does not use, which caps the workgroups a compute unit holds.
 struct Motion {
   Order order;
-  bool nt;
+  bool ntl, nts;
   size_t lds;
 };
 
@@ -312,6 +311,8 @@ constexpr int64_t kCachedInput = 64 << 20;
 // From here (786K matrices, 12 workgroups per compute unit) the cap's extra
 // rounds are many enough not to leave compute units idle in the last one.
 constexpr int64_t kManyBlocks = 3072;
+// FP64 vectors in SoA planes on 128-byte lines store with the hint from here.
+constexpr int64_t kHintedStores = 1024;
 
 // The rules, each with both sides measured (us; three sets of buffers in
 // turn, N(0,1) matrices):
@@ -347,10 +348,14 @@ constexpr int64_t kManyBlocks = 3072;
 //    against 11.2, 500,003 9.3 either way, 300,489 8.2 against 7.5); three
 //    planes of eigenvalues alone lose little to it and keep the hints (FP64
 //    30 M 380 against 384).
-//  * FP64 vectors below kManyBlocks take the plain accesses for any planes:
-//    inputs and results of such a batch stay in the caches (400,000: 10.4
-//    against 14.8).  The chunked order pays from 1280 blocks (400,000: 10.4
-//    against 11.5; 300,001: 9.0 against 8.7).
+//  * FP64 vectors below kManyBlocks load without the hint for any planes, as
+//    the inputs of such a batch stay in the caches.  Planes off the lines are
+//    also stored without it (400,003: 10.4 against 14.8) and take the chunks
+//    from 1280 blocks (400,003: 10.4 against 11.5; 300,001: 9.0 against 8.7);
+//    planes on the lines are stored with it, in chunks, from kHintedStores on
+//    (mean of N(0,1), SPD and stress-mix matrices over 1 and 4 sets of buffers
+//    in turn, against no hint: 300,000 7.9 against 9.0, 500,000 12.3 against
+//    14.1, 650,000 16.5 against 18.4; with both hints 8.6, 14.4 and 18.7).
 //  * Otherwise the hints: FP64 vectors 2^24 393 against 406 without.  The
 //    order is launch order (60 M: 1458, in chunks of 256 tiles 1569), but
 //    for AoS FP64 vectors chunks of 32 (2^24: 390 against 399; 60 M: 1406
@@ -380,11 +385,11 @@ static Motion motion(int64_t blocks, const void* A, Strides ld, int layout, cons
   const bool valu = flags & (kFlagNewton | kFlagPaperBG);
   const bool many = blocks >= kManyBlocks;
   if (layout != 0) {
-    if (!kHbmBound) return Motion{launch, true, 0};
+    if (!kHbmBound) return Motion{launch, true, true, 0};
     const int64_t in_bytes = blocks * kBlock * (layout == 1 ? 6 : 9) * (int64_t)sizeof(T);
     const bool cached = in_bytes <= kCachedInput;
     const size_t lds = blocks >= 16384 ? kLdsFor3 : blocks >= 2560 ? kLdsFor5 : kAosLds<T>;
-    return Motion{chunked_order(blocks, 5), !cached, valu ? 0 : lds - kAosLds<T>};
+    return Motion{chunked_order(blocks, 5), !cached, true, valu ? 0 : lds - kAosLds<T>};
   }
   // the planes' distance is within 64 KB of a multiple of 2^log2 bytes
   const auto near = [&](int log2) {
@@ -393,19 +398,20 @@ static Motion motion(int64_t blocks, const void* A, Strides ld, int layout, cons
   };
   const bool aliased = FORM != kFormF32R && near(FORM == kFormF64 ? 29 : 28);
   if (!VECS)
-    return Motion{FORM == kFormF64 && aliased ? chunked_order(blocks, 8) : launch, true, 0};
+    return Motion{FORM == kFormF64 && aliased ? chunked_order(blocks, 8) : launch, true, true, 0};
   const uintptr_t bits = (uintptr_t)A | (uintptr_t)lambda | (uintptr_t)V |
                          (uintptr_t)(ld.a | ld.l | ld.v) * sizeof(T);
   const bool ragged = (bits & 127u) != 0;
   if (kHbmBound ? ragged || !many : ragged && blocks >= 2048)
-    return Motion{blocks >= 1280 ? chunked_order(blocks, 5) : launch, false,
+    return Motion{blocks >= (ragged ? 1280 : kHintedStores) ? chunked_order(blocks, 5) : launch,
+                  false, !ragged && blocks >= kHintedStores,
                   kHbmBound && many && !valu ? kLdsFor3 : 0};
   const uint32_t chunk = kHbmBound && near(31) ? 5 : 8;
-  return Motion{aliased ? chunked_order(blocks, chunk) : launch, true,
+  return Motion{aliased ? chunked_order(blocks, chunk) : launch, true, true,
                 kHbmBound && !valu ? kLdsFor3 : 0};
 }
 
-template <int FORM, bool VECS, bool INFO, bool NT>
+template <int FORM, bool VECS, bool INFO, bool NTL, bool NTS>
 static void launch_soa(int64_t n, const void* A, Strides ld, void* lambda, void* V,
                        uint32_t flags, const Motion& m, int32_t* info, dim3 grid, dim3 block,
                        hipStream_t stream) {
@@ -415,10 +421,10 @@ static void launch_soa(int64_t n, const void* A, Strides ld, void* lambda, void*
   for (int j = 0; j < 3; ++j) P.l[j] = (T*)lambda + j * ld.l;
   for (int k = 0; k < 9; ++k) P.v[k] = VECS ? (T*)V + k * ld.v : nullptr;
   if ((uint64_t)n * sizeof(T) <= (uint64_t)UINT32_MAX)
-    hipLaunchKernelGGL((k_syev3_soa32<FORM, VECS, INFO, NT>), grid, block, m.lds, stream,
+    hipLaunchKernelGGL((k_syev3_soa32<FORM, VECS, INFO, NTL, NTS>), grid, block, m.lds, stream,
                        (uint32_t)n, P, flags, m.order, info);
-  else
-    hipLaunchKernelGGL((k_syev3_soa<FORM, VECS, INFO, NT>), grid, block, m.lds, stream, n, P,
+  else  // (a batch of this size has both hints or neither)
+    hipLaunchKernelGGL((k_syev3_soa<FORM, VECS, INFO, NTL>), grid, block, m.lds, stream, n, P,
                        flags, m.order, info);
 }
 
@@ -431,13 +437,17 @@ static hipError_t launch_t(int64_t n, const void* A, Strides ld, int layout,
   const dim3 grid((unsigned)blocks), block(kBlock);
   const Motion m = motion<FORM, VECS>(blocks, A, ld, layout, lambda, V, flags);
   if (layout == 0) {
-    // eigenvalues alone always take the hints
-    if (m.nt || !VECS)
-      launch_soa<FORM, VECS, INFO, true>(n, A, ld, lambda, V, flags, m, info, grid, block,
-                                         stream);
-    else
-      launch_soa<FORM, VECS, INFO, !VECS>(n, A, ld, lambda, V, flags, m, info, grid, block,
-                                          stream);
+    const auto launch = [&](auto ntl, auto nts) {
+      launch_soa<FORM, VECS, INFO, decltype(ntl)::value, decltype(nts)::value>(
+          n, A, ld, lambda, V, flags, m, info, grid, block, stream);
+    };
+    using Hint = std::true_type;
+    // eigenvalues alone always take both hints, FP32 storage both or neither
+    using Plain = std::bool_constant<!VECS>;
+    using PlainLoads = std::bool_constant<!(FORM == kFormF64 && VECS)>;
+    if (m.ntl) launch(Hint(), Hint());
+    else if (m.nts) launch(PlainLoads(), Hint());
+    else launch(Plain(), Plain());
   } else {
     // FP64 with vectors alone has plain loads
     constexpr bool kPlain = FORM == kFormF64 && VECS;
@@ -445,7 +455,7 @@ static hipError_t launch_t(int64_t n, const void* A, Strides ld, int layout,
       hipLaunchKernelGGL(kernel, grid, block, m.lds, stream, n, (const T*)A, (T*)lambda, (T*)V,
                          flags, m.order, info);
     };
-    const bool nt = m.nt || !kPlain;
+    const bool nt = m.ntl || !kPlain;
     if (layout == 1) {
       if (nt) launch(k_syev3_aos<FORM, 6, VECS, INFO, true>);
       else launch(k_syev3_aos<FORM, 6, VECS, INFO, !kPlain>);

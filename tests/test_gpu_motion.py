@@ -144,3 +144,17 @@ def test_64_bit_offsets_with_aligned_planes():
         assert torch.equal(v[:, i:i + m], V[:, :m]), i
     del l, v
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32], ids=["f64", "f32"])
+@pytest.mark.parametrize("n", [1023 * BLOCK, 1023 * BLOCK + 16, 1024 * BLOCK, 1024 * BLOCK + 32])
+def test_hinted_stores(n, dtype):
+    """FP64 around the size from which planes on 128-byte lines are stored
+    with the non-temporal hint (1024 blocks), beside planes off them."""
+    A, _ = gen.stress_mix(n, 67, "cuda")
+    A = A.to(dtype).contiguous()
+    lam, V = _pieces(A)
+    for ld, first in (((n + 31) // 32 * 32, 0), (n, 0), (n + 1, 0), (n, 1)):
+        out = (_strided(3, n, ld, first, dtype), _strided(9, n, ld, first, dtype))
+        l, v = s3.syev3(A, out=out)
+        assert torch.equal(l, lam) and torch.equal(v, V), (ld, first)
