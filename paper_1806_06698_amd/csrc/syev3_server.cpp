@@ -172,39 +172,49 @@ Request* lookup(syev3_server* s, int64_t id, int* slot_out) {
   return r;
 }
 
-// The address range [p, p + bytes) lies in one pinned host allocation that
-// the device reaches at the same address and keeps coherent.
-bool device_reaches(int device, const void* p, size_t bytes) {
+// The bytes from p to the end of its pinned host allocation, if the device
+// reaches that at the same address and keeps it coherent; else 0.
+size_t bytes_reached(int device, const void* p) {
   hipPointerAttribute_t at{};
   void* base = nullptr;
   size_t size = 0;
+  if (!p) return 0;
   if (hipPointerGetAttributes(&at, p) != hipSuccess || at.type != hipMemoryTypeHost ||
       at.devicePointer != p || at.isManaged || (at.allocationFlags & hipHostMallocNonCoherent) ||
       (at.device != device && !(at.allocationFlags & hipHostMallocPortable)) ||
       hipMemGetAddressRange((hipDeviceptr_t*)&base, &size, (hipDeviceptr_t)p) != hipSuccess) {
     (void)hipGetLastError();  // pageable memory is no error here
-    return false;
+    return 0;
   }
   const uintptr_t off = (uintptr_t)p - (uintptr_t)base;
-  return off <= size && bytes <= size - off;
+  return off <= size ? size - off : 0;
 }
 
 bool overlap(const void* a, size_t na, const void* b, size_t nb) {
   return (uintptr_t)a < (uintptr_t)b + nb && (uintptr_t)b < (uintptr_t)a + na;
 }
 
+// A host-staged request's buffers with the bytes that the device reaches of
+// each.
+struct HostBuffers {
+  const void* A;
+  void *lam, *V;
+  size_t nA, nlam, nV;
+};
+
 // Whether the kernel may take a host-staged request's buffers as they are:
 // pinned, of aligned values, and no result's memory shared with the input's
 // or another result's (copies finish reading before the results are
 // written, and write the vectors last).
-bool takes_direct(int device, int64_t n, int dtype, const void* A, void* lam, void* V) {
-  const size_t es = dtype == SYEV3_F64 ? 8 : 4;
-  const size_t plane = (size_t)n * es, bA = 6 * plane, bl = 3 * plane, bV = V ? 9 * plane : 0;
-  if (((uintptr_t)A | (uintptr_t)lam | (uintptr_t)V) % es) return false;
-  if (overlap(A, bA, lam, bl) || (V && (overlap(A, bA, V, bV) || overlap(lam, bl, V, bV))))
+bool takes_direct(const Request& r, const HostBuffers& h) {
+  const size_t es = r.dtype == SYEV3_F64 ? 8 : 4;
+  void* V = r.vecs ? h.V : nullptr;
+  const size_t plane = (size_t)r.n * es, bA = 6 * plane, bl = 3 * plane, bV = V ? 9 * plane : 0;
+  if (((uintptr_t)h.A | (uintptr_t)h.lam | (uintptr_t)V) % es) return false;
+  if (overlap(h.A, bA, h.lam, bl) ||
+      (V && (overlap(h.A, bA, V, bV) || overlap(h.lam, bl, V, bV))))
     return false;
-  return device_reaches(device, A, bA) && device_reaches(device, lam, bl) &&
-         (!V || device_reaches(device, V, bV));
+  return bA <= h.nA && bl <= h.nlam && (!V || bV <= h.nV);
 }
 
 }  // namespace
@@ -645,29 +655,16 @@ int syev3_server_submit_host(syev3_server* s, int64_t id, const void* host_A,
                              void* host_lambda, void* host_V) {
   if (!s) return SYEV3_E_STATE;
   if (!host_A || !host_lambda) return SYEV3_E_NULL;
-  int64_t n;
-  int dtype;
-  // a view's input is the caller's device memory: there is nothing to stage
-  const auto admitted = [&](int* slot) {
-    Request* r = lookup(s, id, slot);
-    return r && r->state == kAdmitted && !r->view ? r : nullptr;
-  };
-  {
-    std::lock_guard<std::mutex> lk(s->mu);
-    const Request* r = admitted(nullptr);
-    if (!r) return SYEV3_E_STATE;
-    n = r->n;
-    dtype = r->dtype;
-    if (!r->vecs) host_V = nullptr;
-  }
-  // These queries may wait for the runtime's own locks: not under the
-  // server's, which every other client and the scheduler need.
-  const bool direct = takes_direct(s->device, n, dtype, host_A, host_lambda, host_V);
+  // These queries may wait for the runtime's own locks: before the server's
+  // is taken, which every other client and the scheduler need.
+  const HostBuffers h{host_A, host_lambda, host_V, bytes_reached(s->device, host_A),
+                      bytes_reached(s->device, host_lambda), bytes_reached(s->device, host_V)};
   {
     std::lock_guard<std::mutex> lk(s->mu);
     int slot;
-    Request* r = admitted(&slot);
-    if (!r) return SYEV3_E_STATE;  // submitted or released meanwhile
+    Request* r = lookup(s, id, &slot);
+    // a view's input is the caller's device memory: there is nothing to stage
+    if (!r || r->state != kAdmitted || r->view) return SYEV3_E_STATE;
     try {
       s->queue.push_back(slot);
     } catch (const std::bad_alloc&) {
@@ -677,8 +674,8 @@ int syev3_server_submit_host(syev3_server* s, int64_t id, const void* host_A,
     r->ready = nullptr;
     r->h_A = host_A;
     r->h_lam = host_lambda;
-    r->h_V = host_V;
-    r->direct = direct;
+    r->h_V = r->vecs ? host_V : nullptr;
+    r->direct = takes_direct(*r, h);
     r->t_submit = Clock::now();
     s->note_queue();
     s->st.submitted++;
