@@ -75,8 +75,9 @@ struct Planes {
 };
 
 // T = double: FP64 path.  T = float: FP32 storage with FP64 refinement.
-// 64-bit element offsets, for planes of more than 2^32 bytes.
-template <int FORM, bool VECS, bool INFO, bool NT>
+// 64-bit element offsets, for planes of more than 2^32 bytes.  NTL, NTS: the
+// loads' and the stores' hint.
+template <int FORM, bool VECS, bool INFO, bool NTL, bool NTS>
 __global__ __launch_bounds__(kBlock) void k_syev3_soa(int64_t n, Planes<Storage<FORM>> P,
                                                      uint32_t flags, Order order,
                                                      int32_t* __restrict__ info) {
@@ -85,22 +86,22 @@ __global__ __launch_bounds__(kBlock) void k_syev3_soa(int64_t n, Planes<Storage<
   if (i >= n) return;
   double a[6];
 #pragma unroll
-  for (int k = 0; k < 6; ++k) a[k] = (double)ld<NT>(P.a[k] + i);
+  for (int k = 0; k < 6; ++k) a[k] = (double)ld<NTL>(P.a[k] + i);
   double l[3], v[9];
   bool bad;
   const int code = solve3<VECS, FORM>(a, flags, l, v, bad);
 #pragma unroll
-  for (int j = 0; j < 3; ++j) st<NT>((T)l[j], P.l[j] + i);
+  for (int j = 0; j < 3; ++j) st<NTS>((T)l[j], P.l[j] + i);
   if (VECS) {
 #pragma unroll
-    for (int k = 0; k < 9; ++k) st<NT>((T)v[k], P.v[k] + i);
+    for (int k = 0; k < 9; ++k) st<NTS>((T)v[k], P.v[k] + i);
   }
   if (bad) {  // a NaN or infinite entry: NaN in every output of the matrix
 #pragma unroll
-    for (int j = 0; j < 3; ++j) st<NT>(qnan<T>(), P.l[j] + i);
+    for (int j = 0; j < 3; ++j) st<NTS>(qnan<T>(), P.l[j] + i);
     if (VECS) {
 #pragma unroll
-      for (int k = 0; k < 9; ++k) st<NT>(qnan<T>(), P.v[k] + i);
+      for (int k = 0; k < 9; ++k) st<NTS>(qnan<T>(), P.v[k] + i);
     }
   }
   if (INFO) info[i] = code;
@@ -108,7 +109,7 @@ __global__ __launch_bounds__(kBlock) void k_syev3_soa(int64_t n, Planes<Storage<
 
 // The same with a 32-bit byte offset per lane, for n * sizeof(T) < 2^32:
 // loads and stores take the scalar-base addressing form and need no 64-bit
-// address arithmetic per lane.  NTL, NTS: the loads' and the stores' hint.
+// address arithmetic per lane.
 template <int FORM, bool VECS, bool INFO, bool NTL, bool NTS>
 __global__ __launch_bounds__(kBlock) void k_syev3_soa32(uint32_t n, Planes<Storage<FORM>> P,
                                                        uint32_t flags, Order order,
@@ -359,16 +360,19 @@ constexpr int64_t kHintedStores = 1024;
 //  * Otherwise the hints: FP64 vectors 2^24 393 against 406 without.  The
 //    order is launch order (60 M: 1458, in chunks of 256 tiles 1569), but
 //    for AoS FP64 vectors chunks of 32 (2^24: 390 against 399; 60 M: 1406
-//    against 1475) and, where the plane stride comes within 64 KB of a multiple of 2^29
-//    bytes, so that all planes meet the same channels at once, chunks of
-//    256.  How bad that is depends on where the pages of an allocation lie:
-//    2^26, 16 allocations on two devices, mean 1690, worst 1870 (with 2
-//    workgroups per compute unit 1705 and 1883, with 4 1710 and 1863); N(0,1)
-//    1733 and 1851, without the cap 1800 and 1904, in launch order 1848 and
-//    2003.  2^26 + 4096: 1696 against 1796 in launch order; 2^27: 3493
-//    against 3718.  Where the multiple is one of 2^31 chunks of 32 do better:
-//    2^28 mean of four allocations 6030, in chunks of 256 6703, in launch
-//    order 6291 (at 2^27 3481, no clear gain).
+//    against 1475).
+//  * Where the plane stride comes within 64 KB of a multiple of 2^29 bytes,
+//    all planes meet the same channels at once; how bad that is depends on
+//    where the pages of an allocation lie.  FP64 vectors take chunks of 256
+//    and load without the hint there.  Mean and worst of six allocations, the
+//    first a fresh process's (SPD; N(0,1)): 2^26 1637 and 1678; 1658 and 1665,
+//    with the hint 1668 and 1776; 1719 and 1795, in launch order 1727 and
+//    1842; 1705 and 1757 (chunks of 64: 1776, of 512 with plain loads 1686;
+//    with 2 workgroups per compute unit 1709, with 4 and chunks of 64 1862);
+//    2^26 + 4096 1681, with the hint 1682, in launch order 1834; 2^27 3409
+//    and 3514, with the hint 3597 and 3862.  Where the multiple is one of
+//    2^31 chunks of 32 do better, with the hint or without: 2^28 6776, in
+//    chunks of 256 7211 (plain loads 7001), in launch order 7072.
 //    FP64 eigenvalues alone take the chunks of 256 (2^26: 761 against 820;
 //    2^26 + 4096: 773 against 825; 2^27: 1517 against 1695; but 2^25, 2^28
 //    bytes: 410 against 370), and the unrefined FP32 form does at 2^28 bytes
@@ -406,8 +410,9 @@ static Motion motion(int64_t blocks, const void* A, Strides ld, int layout, cons
     return Motion{blocks >= (ragged ? 1280 : kHintedStores) ? chunked_order(blocks, 5) : launch,
                   false, !ragged && blocks >= kHintedStores,
                   kHbmBound && many && !valu ? kLdsFor3 : 0};
-  const uint32_t chunk = kHbmBound && near(31) ? 5 : 8;
-  return Motion{aliased ? chunked_order(blocks, chunk) : launch, true, true,
+  const bool far = kHbmBound && near(31);
+  return Motion{aliased ? chunked_order(blocks, far ? 5 : 8) : launch,
+                !(kHbmBound && aliased && !far && !valu), true,
                 kHbmBound && !valu ? kLdsFor3 : 0};
 }
 
@@ -423,9 +428,9 @@ static void launch_soa(int64_t n, const void* A, Strides ld, void* lambda, void*
   if ((uint64_t)n * sizeof(T) <= (uint64_t)UINT32_MAX)
     hipLaunchKernelGGL((k_syev3_soa32<FORM, VECS, INFO, NTL, NTS>), grid, block, m.lds, stream,
                        (uint32_t)n, P, flags, m.order, info);
-  else  // (a batch of this size has both hints or neither)
-    hipLaunchKernelGGL((k_syev3_soa<FORM, VECS, INFO, NTL>), grid, block, m.lds, stream, n, P,
-                       flags, m.order, info);
+  else
+    hipLaunchKernelGGL((k_syev3_soa<FORM, VECS, INFO, NTL, NTS>), grid, block, m.lds, stream, n,
+                       P, flags, m.order, info);
 }
 
 template <int FORM, bool VECS, bool INFO>

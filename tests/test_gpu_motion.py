@@ -125,12 +125,14 @@ def test_unrefined_fp32_planes_a_quarter_gigabyte_apart():
         torch.cuda.empty_cache()
 
 
-def test_64_bit_offsets_with_aligned_planes():
+@pytest.mark.parametrize("n", [(1 << 29) + 64, (1 << 29) + (1 << 26)])
+def test_64_bit_offsets_with_aligned_planes(n):
     """Planes of more than 2^32 bytes, all on 128-byte lines: the hinted
-    variant of the kernel with 64-bit offsets (an odd count takes the plain
-    one).  The input repeats one piece, and every repeat equals it."""
+    variants of the kernel with 64-bit offsets (an odd count takes the plain
+    one), with planes a multiple of 2^31 bytes apart and one of 2^29 alone,
+    which loads without the hint.  The input repeats one piece, and every
+    repeat equals it."""
     piece = 1 << 20
-    n = (1 << 29) + 64
     base, _ = gen.stress_mix(piece, 66, "cuda")
     lam, V = s3.syev3(base)
     A = torch.empty(6, n, dtype=torch.float64, device="cuda")
